@@ -356,107 +356,142 @@ inline int grid_for(int64_t work, int per_block = 256, int cap = 65535) {
 
 
 // ---------------------------------------------------------------- greedy commit
-// One workgroup per row: the index of the largest element by order_key (NaN
-// lowest, -0 == +0), the lowest index among equal keys.  out[row] = index and,
-// with commit_pos, ids[commit_pos[row]] = index (an out-of-range position is
+// One workgroup per row: the index of the largest element (NaN below
+// everything, -0 == +0), the lowest index among equal values, and, with conf,
+// the softmax probability of the largest.  out[row] = index and, with
+// commit_pos, ids[commit_pos[row]] = index (an out-of-range position is
 // skipped).
-__device__ __forceinline__ void argmax_take(uint32_t key, int idx, uint32_t& bk, int& bi) {
-  if (key > bk || (key == bk && idx < bi)) {
-    bk = key;
-    bi = idx;
-  }
-}
-__device__ __forceinline__ uint32_t elem_bits(bf16 v) { return (uint32_t)__builtin_bit_cast(uint16_t, v) << 16; }
-__device__ __forceinline__ uint32_t elem_bits(float v) { return __builtin_bit_cast(uint32_t, v); }
+//
+// Bound by the read of the logits.  A thread walks 16-byte chunks in
+// ascending order, kArgUnroll of them in flight, and keeps its maximum, the
+// first chunk that reached it and, with conf, sum exp(x - max); only a chunk
+// that raises the maximum branches (rare after the first few), every other
+// element costs one exponential and a handful of plain operations.  The
+// index inside the winning chunk is looked up at the end.  256 rows of 126,464
+// bf16 logits: 129 us with a branch per element and 256 threads a row, 22 us
+// with this and 1024 threads (65 MB at 3.0 TB/s).
+constexpr int kArgUnroll = 4;
 
-// Online softmax sum: (m, s) with s = sum exp(x - m) over the finite values
-// seen (NaN and -inf add nothing); combining rescales the smaller maximum.
-__device__ __forceinline__ void softmax_add(float x, float& m, float& s) {
-  if (!(x > -INFINITY)) return;  // NaN or -inf
-  if (x > m) {
-    s = s * __expf(m - x) + 1.f;
-    m = x;
-  } else if (x == m) {
-    s += 1.f;  // exact, also for an infinite maximum
+__device__ __forceinline__ float nan_low(float v) { return fmaxf(v, -INFINITY); }
+
+// exp(x - m) for x <= m, with x == m giving 1 exactly (also for +inf) and
+// x == -inf giving 0; m > -inf.  bf16 takes +inf as the largest fp32, which
+// no finite bf16 equals and which subtracts from itself to 0.
+template <typename T>
+__device__ __forceinline__ float soft_term(float x, float m) {
+  if constexpr (sizeof(T) == 2) {
+    return __expf(fminf(x, 3.4028234663852886e38f) - fminf(m, 3.4028234663852886e38f));
   } else {
-    s += __expf(x - m);
-  }
-}
-__device__ __forceinline__ void softmax_merge(float m2, float s2, float& m, float& s) {
-  if (s2 == 0.f) return;
-  if (s != 0.f && m2 == m) {
-    s += s2;
-    return;
-  }
-  if (s == 0.f || m2 > m) {
-    s = s2 + (s == 0.f ? 0.f : s * __expf(m - m2));
-    m = m2;
-  } else {
-    s += s2 * __expf(m2 - m);
+    return x == m ? 1.f : __expf(x - m);
   }
 }
 
 template <typename T>
-__global__ __launch_bounds__(256) void argmax_commit_kernel(const T* __restrict__ x, int64_t ld, int n, int vec,
-                                                            int32_t* __restrict__ out, float* __restrict__ conf,
-                                                            const int32_t* __restrict__ commit_pos,
-                                                            int32_t* __restrict__ ids, int64_t ids_len) {
+__global__ __launch_bounds__(1024) void argmax_commit_kernel(const T* __restrict__ x, int64_t ld, int n, int vec,
+                                                             int32_t* __restrict__ out, float* __restrict__ conf,
+                                                             const int32_t* __restrict__ commit_pos,
+                                                             int32_t* __restrict__ ids, int64_t ids_len) {
   constexpr int PER = 16 / sizeof(T);
   const int64_t row = blockIdx.x;
   const T* xr = x + row * ld;
-  uint32_t bk = 0u;
-  int bi = 0x7FFFFFFF;
-  float sm = -INFINITY, ss = 0.f;
-  int start = 0;
-  if (vec) {
-    const int chunks = n / PER;
-    for (int c = threadIdx.x; c < chunks; c += 256) {
-      const u32x4 raw = *reinterpret_cast<const u32x4*>(xr + (int64_t)c * PER);
-      T v[PER];
-      __builtin_memcpy(v, &raw, 16);
+  const int tid = threadIdx.x, nt = blockDim.x;
+  const int chunks = vec ? n / PER : 0;  // whole 16-byte chunks; the rest one element at a time
+  float m = -INFINITY, s = 0.f;
+  int first = -1;  // this thread's first chunk (or, from `chunks` on, element) holding m
+  auto take = [&](const auto& v, int at) {
+    constexpr int N = sizeof(v) / sizeof(float);
+    float cm = v[0];
 #pragma unroll
-      for (int j = 0; j < PER; ++j) {
-        argmax_take(order_key(elem_bits(v[j])), c * PER + j, bk, bi);
-        if (conf) softmax_add(to_f32(v[j]), sm, ss);
+    for (int j = 1; j < N; ++j) cm = fmaxf(cm, v[j]);
+    if (cm > m) {
+      s = s == 0.f ? 0.f : s * __expf(m - cm);
+      m = cm;
+      first = at;
+    }
+    if (conf && m > -INFINITY) {
+#pragma unroll
+      for (int j = 0; j < N; ++j) s += soft_term<T>(v[j], m);
+    }
+  };
+  auto unpack = [&](const u32x4& raw, float (&v)[PER]) {
+    T t[PER];
+    __builtin_memcpy(t, &raw, 16);
+#pragma unroll
+    for (int j = 0; j < PER; ++j) v[j] = nan_low(to_f32(t[j]));
+  };
+  const u32x4* xc = reinterpret_cast<const u32x4*>(xr);
+  int c = tid;
+  for (; c + (kArgUnroll - 1) * nt < chunks; c += kArgUnroll * nt) {
+    u32x4 raw[kArgUnroll];
+#pragma unroll
+    for (int u = 0; u < kArgUnroll; ++u) raw[u] = xc[c + u * nt];
+#pragma unroll
+    for (int u = 0; u < kArgUnroll; ++u) {
+      float v[PER];
+      unpack(raw[u], v);
+      take(v, c + u * nt);
+    }
+  }
+  for (; c < chunks; c += nt) {
+    const u32x4 raw = xc[c];
+    float v[PER];
+    unpack(raw, v);
+    take(v, c);
+  }
+  for (int i = chunks * PER + tid; i < n; i += nt) {
+    const float v[1] = {nan_low(to_f32(xr[i]))};
+    take(v, chunks + i - chunks * PER);
+  }
+
+  // the row's maximum, its lowest index, and the sum relative to it
+  __shared__ float sm[16], ss[16];
+  __shared__ int si[16];
+  const int lane = tid & 63, wave = tid >> 6, waves = (nt + 63) >> 6;
+  const float wm = wave_max(m);
+  if (lane == 0) sm[wave] = wm;
+  __syncthreads();
+  float M = sm[0];
+  for (int w = 1; w < waves; ++w) M = fmaxf(M, sm[w]);
+  int idx = 0x7FFFFFFF;
+  if (M > -INFINITY) {
+    if (m == M) {
+      if (first >= chunks) {
+        idx = chunks * PER + (first - chunks);
+      } else {
+        float v[PER];
+        unpack(xc[first], v);
+#pragma unroll
+        for (int j = PER - 1; j >= 0; --j)
+          if (v[j] == M) idx = first * PER + j;
       }
     }
-    start = chunks * PER;
+    s = s == 0.f ? 0.f : m == M ? s : s * __expf(m - M);
+  } else {
+    // nothing above -inf: the first -inf, or 0 in a row of NaN
+    for (int i = tid; i < n && idx == 0x7FFFFFFF; i += nt)
+      if (to_f32(xr[i]) == -INFINITY) idx = i;
+    s = 0.f;
   }
-  for (int i = start + threadIdx.x; i < n; i += 256) {
-    argmax_take(order_key(elem_bits(xr[i])), i, bk, bi);
-    if (conf) softmax_add(to_f32(xr[i]), sm, ss);
-  }
+  s = wave_sum(s);
 #pragma unroll
-  for (int o = 32; o > 0; o >>= 1) {
-    const uint32_t ok = __shfl_xor(bk, o);
-    const int oi = __shfl_xor(bi, o);
-    argmax_take(ok, oi, bk, bi);
-    const float om = __shfl_xor(sm, o), os = __shfl_xor(ss, o);
-    softmax_merge(om, os, sm, ss);
-  }
-  __shared__ uint32_t sk[4];
-  __shared__ int si[4];
-  __shared__ float smm[4], sss[4];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  for (int o = 32; o > 0; o >>= 1) idx = min(idx, __shfl_xor(idx, o));
   if (lane == 0) {
-    sk[wave] = bk;
-    si[wave] = bi;
-    smm[wave] = sm;
-    sss[wave] = ss;
+    ss[wave] = s;
+    si[wave] = idx;
   }
   __syncthreads();
-  if (threadIdx.x == 0) {
-#pragma unroll
-    for (int w = 1; w < 4; ++w) {
-      argmax_take(sk[w], si[w], bk, bi);
-      softmax_merge(smm[w], sss[w], sm, ss);
+  if (tid == 0) {
+    float tot = 0.f;
+    for (int w = 0; w < waves; ++w) {
+      tot += ss[w];
+      idx = min(idx, si[w]);
     }
-    out[row] = bi;
-    // probability of the largest finite logit (the argmax unless the row has +inf or only NaN)
-    if (conf) conf[row] = ss > 0.f ? 1.f / ss : 0.f;
+    if (idx == 0x7FFFFFFF) idx = 0;
+    out[row] = idx;
+    if (conf) conf[row] = tot > 0.f ? 1.f / tot : 0.f;
     if (commit_pos) {
       const int64_t p = commit_pos[row];
-      if (p >= 0 && p < ids_len) ids[p] = bi;
+      if (p >= 0 && p < ids_len) ids[p] = idx;
     }
   }
 }
@@ -702,11 +737,13 @@ hipError_t launch_argmax_commit(acache_dtype dt, const void* x, int64_t ld, int 
                                float* conf, const int32_t* commit_pos, int32_t* ids, int64_t ids_len, hipStream_t s) {
   const int es = dt == ACACHE_BF16 ? 2 : 4;
   const int vec = ((uintptr_t)x % 16 == 0 && (ld * es) % 16 == 0) ? 1 : 0;
+  // 1024 threads where every one has at least two 16-byte chunks to read
+  const int threads = (int64_t)n * es >= 32768 ? 1024 : 256;
   if (dt == ACACHE_BF16)
-    hipLaunchKernelGGL(argmax_commit_kernel<bf16>, dim3(rows), dim3(256), 0, s, (const bf16*)x, ld, n, vec, out,
+    hipLaunchKernelGGL(argmax_commit_kernel<bf16>, dim3(rows), dim3(threads), 0, s, (const bf16*)x, ld, n, vec, out,
                        conf, commit_pos, ids, ids_len);
   else
-    hipLaunchKernelGGL(argmax_commit_kernel<float>, dim3(rows), dim3(256), 0, s, (const float*)x, ld, n, vec, out,
+    hipLaunchKernelGGL(argmax_commit_kernel<float>, dim3(rows), dim3(threads), 0, s, (const float*)x, ld, n, vec, out,
                        conf, commit_pos, ids, ids_len);
   return hipGetLastError();
 }
