@@ -1,7 +1,13 @@
 // fp32 path of the recompute block.  On gfx950 the fp32 matrix and fp32
-// vector peaks are equal (157 TFLOP/s), so the fp32 contractions use LDS-tiled
-// vector FMA instead of the 32x32x2 fp32 MFMA.  Rotary angles are reduced in
+// vector peaks are equal (157 TFLOP/s); what the fp32 MFMA (16x16x4, products
+// and sums in fp32) saves is operand traffic: a lane's 16-byte loads along the
+// contraction feed it as they are, so the small products, the attention and
+// the scores need no staging of their operands and split the contraction (or
+// the keys) over the waves of a workgroup.  Rotary angles are reduced in
 // fp64 so the fp32 outputs stay within a few ulp at any position.
+#include <algorithm>
+#include <type_traits>
+
 #include "device.h"
 #include "internal.h"
 
@@ -69,6 +75,78 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(const float* __restrict__
     }
 }
 
+// ---------------------------------------------------------------- small products
+// 16x16x4 fp32 MFMA: lane l supplies A[l % 16][l / 16] and B[l / 16][l % 16]
+// and receives D[4 (l / 16) + r][l % 16], r = 0..3.
+__device__ __forceinline__ f32x4 mfma16x16x4(float a, float b, f32x4 c) {
+  return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
+}
+// p[k .. k + 3], zero from k = n on.  VEC: n % 4 == 0, p 16-byte aligned and
+// k a multiple of 4, so the four are all in or all out.
+template <bool VEC>
+__device__ __forceinline__ f32x4 load4(const float* __restrict__ p, int k, int n) {
+  f32x4 v = {0.f, 0.f, 0.f, 0.f};
+  if constexpr (VEC) {
+    if (k < n) v = *reinterpret_cast<const f32x4*>(p + k);
+  } else {
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+      if (k + i < n) v[i] = p[k + i];
+  }
+  return v;
+}
+
+// A few rows against a few hundred columns: nothing but latency.  One
+// workgroup per 16 x 16 outputs, its 8 waves taking every eighth 16-wide
+// slice of K (4 MFMAs on two 16-byte loads per lane, all of them in flight),
+// their sums added in wave order through LDS.  90 rows, 768 x 256 / 256 x
+// 688: 23 / 60 us with the 64 x 64 tiles above (8 to 44 workgroups, K walked
+// serially), 4.5 / 5.8 us with this.  It re-reads its operands from L2 once per
+// 16 rows, so the larger tiles win where they give every CU one: 512 x 2048 x
+// 512 (256 tiles) takes 33 us here and 47 there, 1024 x 2048 x 1024 (512) 116
+// and 101.
+constexpr int kSmallWaves = 8;
+constexpr int kSmallTiles = 256;  // 64 x 64 tiles up to which this kernel is taken
+
+template <bool VEC>
+__global__ __launch_bounds__(64 * kSmallWaves) void gemm_f32_small_kernel(const float* __restrict__ X,
+                                                                          const float* __restrict__ W,
+                                                                          float* __restrict__ C, int64_t ldc, int M,
+                                                                          int N, int K, int accumulate) {
+  __shared__ f32x4 red[kSmallWaves][64];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int i16 = lane & 15, g = lane >> 4;
+  const int n0 = blockIdx.x * 16, m0 = blockIdx.y * 16;
+  const float* wr = W + (int64_t)min(n0 + i16, N - 1) * K;
+  const float* xr = X + (int64_t)min(m0 + i16, M - 1) * K;
+  f32x4 acc0 = {0.f, 0.f, 0.f, 0.f}, acc1 = acc0;
+#pragma unroll 4
+  for (int k0 = 16 * wave; k0 < K; k0 += 16 * kSmallWaves) {
+    const f32x4 a = load4<VEC>(wr, k0 + 4 * g, K);
+    const f32x4 b = load4<VEC>(xr, k0 + 4 * g, K);
+    acc0 = mfma16x16x4(a[0], b[0], acc0);
+    acc1 = mfma16x16x4(a[1], b[1], acc1);
+    acc0 = mfma16x16x4(a[2], b[2], acc0);
+    acc1 = mfma16x16x4(a[3], b[3], acc1);
+  }
+  red[wave][lane] = acc0 + acc1;
+  __syncthreads();
+  if (wave != 0) return;
+  f32x4 t = red[0][lane];
+#pragma unroll
+  for (int w = 1; w < kSmallWaves; ++w) t += red[w][lane];
+  const int m = m0 + i16;
+  if (m >= M) return;
+#pragma unroll
+  for (int r = 0; r < 4; ++r) {
+    const int n = n0 + 4 * g + r;
+    if (n < N) {
+      float* p = C + (int64_t)m * ldc + n;
+      *p = accumulate ? *p + t[r] : t[r];
+    }
+  }
+}
+
 // ---------------------------------------------------------------- rotary + K/V store
 __global__ __launch_bounds__(256) void rope_scatter_f32_kernel(const float* __restrict__ qkv, int H, int Hkv,
                                                                int dh, const int32_t* __restrict__ pos,
@@ -113,154 +191,272 @@ __global__ __launch_bounds__(256) void swiglu_f32_kernel(const float* __restrict
   h[t] = g / (1.f + expf(-g)) * u;
 }
 
-// ---------------------------------------------------------------- attention (one wave per row and head)
-__device__ __forceinline__ float dot_row(const float* __restrict__ sq, const float* __restrict__ k, int dh) {
-  float s = 0.f;
-  for (int d = 0; d < dh; ++d) s = fmaf(sq[d], k[d], s);
-  return s;
-}
-
+// ---------------------------------------------------------------- attention
 struct RowsArgs {
   int batch;
   int row_start[kMaxBatch + 1];
   int key_start[kMaxBatch + 1];
   int key_len[kMaxBatch + 1];
+  int tile_start[kMaxBatch + 1];  // cumulative 16-row tiles
 };
 
-__device__ __forceinline__ int request_of(const RowsArgs& a, int row) {
+__device__ __forceinline__ int request_of(const RowsArgs& a, int tile) {
   int lo = 0, hi = a.batch - 1;
   while (lo < hi) {
     const int mid = (lo + hi + 1) >> 1;
-    if (a.row_start[mid] <= row) lo = mid; else hi = mid - 1;
+    if (a.tile_start[mid] <= tile) lo = mid; else hi = mid - 1;
   }
   return lo;
 }
 
-// Log-sum-exp (natural) of row `qrow`, head h over the keys named by slots.
-__device__ float row_lse(const float* sq, const int32_t* slots, int S, const float* kp, int64_t pool_ld,
-                         int64_t n_slots, int64_t koff, int dh, float scale) {
-  const int lane = threadIdx.x;
-  float m = -INFINITY, l = 0.f;
-  for (int j = lane; j < S; j += 64) {
-    const int64_t sl = slots[j];
-    const float z = (sl >= 0 && sl < n_slots) ? dot_row(sq, kp + sl * pool_ld + koff, dh) * scale : 0.f;
-    const float mn = fmaxf(m, z);
-    l = l * expf(m - mn) + expf(z - mn);
-    m = mn;
-  }
-  const float M = wave_max(m);
-  l = (m == -INFINITY) ? 0.f : l * expf(m - M);
-  return M + logf(wave_sum(l));
-}
+// 16 query rows of one head per workgroup; its 8 waves take every eighth tile
+// of 16 keys with an online softmax each, merged in wave order through LDS.
+// Keys are the MFMA A operand, so a lane holds four logits of one query and
+// they are the B operand of the product with V as they stand.  A key whose
+// slot is out of range has logit 0 and a zero V row.
+// q_rows (nullable): query row i is row q_rows[i] (zeros where it is outside
+// [0, q_n_rows)).  LSE_ONLY: no output rows, only their log-sum-exp.
+// Latency-bound at the sizes that run in fp32: 90 rows, 4 heads of 64, 192
+// keys took 62 us with a wave per row and head that walked its keys one lane
+// each, 11 us with this.
+constexpr int kAttWaves = 8;
 
-__global__ __launch_bounds__(64) void attention_f32_kernel(RowsArgs a, int H, int Hkv, int dh,
-                                                           const float* __restrict__ q,
-                                                           const int32_t* __restrict__ read_slots,
-                                                           const float* __restrict__ kp,
-                                                           const float* __restrict__ vp, int64_t pool_ld,
-                                                           int64_t n_slots, float* __restrict__ out,
-                                                           float* __restrict__ lse) {
-  __shared__ float sq[128];
-  __shared__ float sp[64];
-  const int row = blockIdx.x, h = blockIdx.y, lane = threadIdx.x;
-  const int b = request_of(a, row);
-  const int g = h / (H / Hkv);
+template <int ND, bool VEC, bool LSE_ONLY>
+__global__ __launch_bounds__(64 * kAttWaves) void attention_f32_kernel(
+    RowsArgs a, int H, int Hkv, int dh, const float* __restrict__ q, int64_t q_ld, int64_t q_n_rows,
+    const int32_t* __restrict__ q_rows, const int32_t* __restrict__ read_slots, const float* __restrict__ kp,
+    const float* __restrict__ vp, int64_t pool_ld, int64_t n_slots, float* __restrict__ out,
+    float* __restrict__ lse) {
+  __shared__ float sm[kAttWaves][16], sl[kAttWaves][16];
+  __shared__ f32x4 so[LSE_ONLY ? 1 : kAttWaves][LSE_ONLY ? 1 : ND][64];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int i16 = lane & 15, g = lane >> 4;
+  const int h = blockIdx.y;
+  const int b = request_of(a, blockIdx.x);
+  const int row0 = a.row_start[b] + (blockIdx.x - a.tile_start[b]) * 16;
+  const int nrow = min(16, a.row_start[b + 1] - row0);
   const int S = a.key_len[b];
   const int32_t* slots = read_slots + a.key_start[b];
-  const int64_t koff = (int64_t)g * dh;
-  for (int d = lane; d < dh; d += 64) sq[d] = q[(int64_t)row * H * dh + h * dh + d];
-  __syncthreads();
+  const int64_t koff = (int64_t)(h / (H / Hkv)) * dh;
   const float scale = rsqrtf((float)dh);
-  const float L = row_lse(sq, slots, S, kp, pool_ld, n_slots, koff, dh, scale);
-  float o0 = 0.f, o1 = 0.f;
-  for (int c = 0; c < S; c += 64) {
-    const int j = c + lane;
-    float pj = 0.f;
-    if (j < S) {
-      const int64_t sl = slots[j];
-      const float z = (sl >= 0 && sl < n_slots) ? dot_row(sq, kp + sl * pool_ld + koff, dh) * scale : 0.f;
-      pj = expf(z - L);
+
+  f32x4 qf[ND];
+  {
+    int64_t r = row0 + min(i16, nrow - 1);
+    if (q_rows) r = q_rows[r];
+    const bool ok = r >= 0 && r < q_n_rows;
+    const float* qr = q + (ok ? r : 0) * q_ld + (int64_t)h * dh;
+#pragma unroll
+    for (int c = 0; c < ND; ++c) {
+      qf[c] = load4<VEC>(qr, 16 * c + 4 * g, dh);
+      if (!ok) qf[c] = f32x4{0.f, 0.f, 0.f, 0.f};
     }
-    sp[lane] = pj;
-    __syncthreads();
-    const int n = min(64, S - c);
-    for (int jj = 0; jj < n; ++jj) {
-      const int64_t sl = slots[c + jj];
-      if (sl < 0 || sl >= n_slots) continue;
-      const float* vr = vp + sl * pool_ld + koff;
-      if (lane < dh) o0 = fmaf(sp[jj], vr[lane], o0);
-      if (lane + 64 < dh) o1 = fmaf(sp[jj], vr[lane + 64], o1);
-    }
-    __syncthreads();
   }
-  float* op = out + (int64_t)row * H * dh + h * dh;
-  if (lane < dh) op[lane] = o0;
-  if (lane + 64 < dh) op[lane + 64] = o1;
-  if (lse && lane == 0) lse[(int64_t)row * H + h] = L;
+  float m = -INFINITY, l = 0.f;  // of query i16 over this wave's keys (l: this lane's share)
+  f32x4 o[ND];
+#pragma unroll
+  for (int c = 0; c < ND; ++c) o[c] = f32x4{0.f, 0.f, 0.f, 0.f};
+  for (int t = wave * 16; t < S; t += 16 * kAttWaves) {
+    int64_t sl16 = t + i16 < S ? slots[t + i16] : -1;
+    if (sl16 < 0 || sl16 >= n_slots) sl16 = -1;
+    const float* kr = kp + (sl16 < 0 ? 0 : sl16) * pool_ld + koff;
+    f32x4 kf[ND];
+#pragma unroll
+    for (int c = 0; c < ND; ++c) {
+      kf[c] = load4<VEC>(kr, 16 * c + 4 * g, dh);
+      if (sl16 < 0) kf[c] = f32x4{0.f, 0.f, 0.f, 0.f};
+    }
+    float vf[LSE_ONLY ? 1 : ND][4];
+    if constexpr (!LSE_ONLY) {
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int vs = __shfl((int)sl16, 4 * g + r);
+        const float* vr = vp + (int64_t)(vs < 0 ? 0 : vs) * pool_ld + koff;
+#pragma unroll
+        for (int c = 0; c < ND; ++c) vf[c][r] = (vs >= 0 && 16 * c + i16 < dh) ? vr[16 * c + i16] : 0.f;
+      }
+    }
+    f32x4 z0 = {0.f, 0.f, 0.f, 0.f}, z1 = z0;
+#pragma unroll
+    for (int c = 0; c < ND; ++c) {
+      z0 = mfma16x16x4(kf[c][0], qf[c][0], z0);
+      z1 = mfma16x16x4(kf[c][1], qf[c][1], z1);
+      z0 = mfma16x16x4(kf[c][2], qf[c][2], z0);
+      z1 = mfma16x16x4(kf[c][3], qf[c][3], z1);
+    }
+    float z[4], mt = m;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      z[r] = t + 4 * g + r < S ? (z0[r] + z1[r]) * scale : -INFINITY;
+      mt = fmaxf(mt, z[r]);
+    }
+    mt = fmaxf(mt, __shfl_xor(mt, 16));
+    mt = fmaxf(mt, __shfl_xor(mt, 32));
+    if (mt > m) {
+      const float f = expf(m - mt);
+      l *= f;
+      if constexpr (!LSE_ONLY) {
+#pragma unroll
+        for (int c = 0; c < ND; ++c) o[c] *= f;
+      }
+      m = mt;
+    }
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      z[r] = expf(z[r] - m);
+      l += z[r];
+    }
+    if constexpr (!LSE_ONLY) {
+#pragma unroll
+      for (int r = 0; r < 4; ++r)
+#pragma unroll
+        for (int c = 0; c < ND; ++c) o[c] = mfma16x16x4(vf[c][r], z[r], o[c]);
+    }
+  }
+  l += __shfl_xor(l, 16);
+  l += __shfl_xor(l, 32);
+  if (g == 0) {
+    sm[wave][i16] = m;
+    sl[wave][i16] = l;
+  }
+  if constexpr (!LSE_ONLY) {
+#pragma unroll
+    for (int c = 0; c < ND; ++c) so[wave][c][lane] = o[c];
+  }
+  __syncthreads();
+  // the tile's keys span at least wave 0, so the merged maximum is a logit
+  float M = sm[0][i16], L = 0.f;
+#pragma unroll
+  for (int w = 1; w < kAttWaves; ++w) M = fmaxf(M, sm[w][i16]);
+  float f[kAttWaves];
+#pragma unroll
+  for (int w = 0; w < kAttWaves; ++w) {
+    f[w] = expf(sm[w][i16] - M);
+    L += sl[w][i16] * f[w];
+  }
+  if (i16 >= nrow) return;
+  const int64_t row = row0 + i16;
+  if (lse && wave == 0 && g == 0) lse[row * H + h] = M + logf(L);
+  if constexpr (!LSE_ONLY) {
+    const float inv = 1.f / L;
+    for (int c = wave; c < ND; c += kAttWaves) {
+      f32x4 t = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int w = 0; w < kAttWaves; ++w) t += so[w][c][lane] * f[w];
+      float* op = out + row * H * dh + (int64_t)h * dh;
+#pragma unroll
+      for (int r = 0; r < 4; ++r)
+        if (16 * c + 4 * g + r < dh) op[16 * c + 4 * g + r] = t[r] * inv;
+    }
+  }
 }
 
 // ---------------------------------------------------------------- probe scores (Eq. 4-5)
-__global__ __launch_bounds__(64) void score_lse_f32_kernel(int H, int Hkv, int dh, const float* __restrict__ q,
-                                                           int64_t q_ld, int64_t q_n_rows,
-                                                           const int32_t* __restrict__ q_rows,
-                                                           const float* __restrict__ kp, int64_t pool_ld,
-                                                           int64_t n_slots, const int32_t* __restrict__ affix_slots,
-                                                           int L, float* __restrict__ lse_out) {
-  __shared__ float sq[128];
-  const int i = blockIdx.x, h = blockIdx.y, lane = threadIdx.x;
-  const int g = h / (H / Hkv);
-  int64_t row = q_rows[i];
-  const bool ok = row >= 0 && row < q_n_rows;
-  for (int d = lane; d < dh; d += 64) sq[d] = ok ? q[row * q_ld + h * dh + d] : 0.f;
-  __syncthreads();
-  const float v = row_lse(sq, affix_slots, L, kp, pool_ld, n_slots, (int64_t)g * dh, dh, rsqrtf((float)dh));
-  if (lane == 0) lse_out[(int64_t)i * H + h] = v;
-}
-
-__global__ __launch_bounds__(64) void score_colsum_f32_kernel(RowsArgs a, int H, int Hkv, int dh,
-                                                              const float* __restrict__ q, int64_t q_ld,
-                                                              int64_t q_n_rows, const int32_t* __restrict__ q_rows,
-                                                              const float* __restrict__ kp, int64_t pool_ld,
-                                                              int64_t n_slots, const int32_t* __restrict__ affix_slots,
-                                                              int L, const float* __restrict__ lse, int lse_by_qrow,
-                                                              float* __restrict__ part) {
-  __shared__ float sq[128];
-  const int kt = blockIdx.x, h = blockIdx.y, b = blockIdx.z, lane = threadIdx.x;
-  const int g = h / (H / Hkv);
-  const int j = kt * 64 + lane;
-  int64_t sl = -1;
-  if (j < L) {
-    sl = affix_slots[j];
-    if (sl < 0 || sl >= n_slots) sl = -1;
-  }
-  const float* krow = kp + (sl < 0 ? 0 : sl) * pool_ld + (int64_t)g * dh;
+// One workgroup per (16 affix keys, head, request); its 8 waves take every
+// eighth tile of 16 masked queries.  Queries are the MFMA A operand, so a
+// lane holds four queries of one key: it adds their weights, and the lanes of
+// a key and then the waves are added in a fixed order.
+template <int ND, bool VEC>
+__global__ __launch_bounds__(64 * kAttWaves) void score_colsum_f32_kernel(
+    RowsArgs a, int H, int Hkv, int dh, const float* __restrict__ q, int64_t q_ld, int64_t q_n_rows,
+    const int32_t* __restrict__ q_rows, const float* __restrict__ kp, int64_t pool_ld, int64_t n_slots,
+    const int32_t* __restrict__ affix_slots, int L, const float* __restrict__ lse, int lse_by_qrow,
+    float* __restrict__ part) {
+  __shared__ float red[kAttWaves][16];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int i16 = lane & 15, g = lane >> 4;
+  const int h = blockIdx.y, b = blockIdx.z;
+  const int j = blockIdx.x * 16 + i16;
+  int64_t sl = j < L ? affix_slots[j] : -1;
+  if (sl < 0 || sl >= n_slots) sl = -1;
+  const float* kr = kp + (sl < 0 ? 0 : sl) * pool_ld + (int64_t)(h / (H / Hkv)) * dh;
+  f32x4 kf[ND];
+#pragma unroll
+  for (int c = 0; c < ND; ++c) kf[c] = load4<VEC>(kr, 16 * c + 4 * g, dh);
   const float scale = rsqrtf((float)dh);
   float acc = 0.f;
-  for (int qi = a.row_start[b]; qi < a.row_start[b + 1]; ++qi) {
-    const int64_t row = q_rows[qi];
-    const bool ok = row >= 0 && row < q_n_rows;
-    __syncthreads();
-    for (int d = lane; d < dh; d += 64) sq[d] = ok ? q[row * q_ld + h * dh + d] : 0.f;
-    __syncthreads();
-    if (!ok || sl < 0) continue;
-    const float z = dot_row(sq, krow, dh) * scale;
-    const float l = lse[(lse_by_qrow ? (int64_t)qi : row) * H + h];
-    acc += expf(z - l);
+  for (int q0 = a.row_start[b] + 16 * wave; q0 < a.row_start[b + 1]; q0 += 16 * kAttWaves) {
+    const int qi = q0 + i16;
+    int64_t row = qi < a.row_start[b + 1] ? q_rows[qi] : -1;
+    if (row < 0 || row >= q_n_rows) row = -1;
+    const float* qr = q + (row < 0 ? 0 : row) * q_ld + (int64_t)h * dh;
+    // a query that is not there weighs nothing
+    const float lq = row < 0 ? INFINITY : lse[(lse_by_qrow ? (int64_t)qi : row) * H + h];
+    f32x4 z0 = {0.f, 0.f, 0.f, 0.f}, z1 = z0;
+#pragma unroll
+    for (int c = 0; c < ND; ++c) {
+      const f32x4 qf = load4<VEC>(qr, 16 * c + 4 * g, dh);
+      z0 = mfma16x16x4(qf[0], kf[c][0], z0);
+      z1 = mfma16x16x4(qf[1], kf[c][1], z1);
+      z0 = mfma16x16x4(qf[2], kf[c][2], z0);
+      z1 = mfma16x16x4(qf[3], kf[c][3], z1);
+    }
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const float lr = __shfl(lq, 4 * g + r);
+      acc += lr == INFINITY ? 0.f : expf((z0[r] + z1[r]) * scale - lr);
+    }
   }
-  if (j < L) part[((int64_t)b * H + h) * L + j] = acc;
+  acc += __shfl_xor(acc, 16);
+  acc += __shfl_xor(acc, 32);
+  if (g == 0) red[wave][i16] = acc;
+  __syncthreads();
+  if (threadIdx.x < 16 && j < L) {
+    float t = red[0][i16];
+#pragma unroll
+    for (int w = 1; w < kAttWaves; ++w) t += red[w][i16];
+    part[((int64_t)b * H + h) * L + j] = sl < 0 ? 0.f : t;
+  }
 }
 
 RowsArgs rows_args(const int* starts, int batch) {
   RowsArgs a = {};
   a.batch = batch;
   for (int b = 0; b <= batch; ++b) a.row_start[b] = starts[b];
+  for (int b = 0; b < batch; ++b) a.tile_start[b + 1] = a.tile_start[b] + (starts[b + 1] - starts[b] + 15) / 16;
   return a;
+}
+
+// f(ND, VEC): ND 16-wide slices of a head; VEC: 16-byte loads along it.
+template <typename F>
+hipError_t by_head_dim(int dh, bool vec, F f) {
+  auto go = [&](auto nd) {
+    if (vec) f(nd, std::true_type());
+    else f(nd, std::false_type());
+  };
+  switch ((dh + 15) / 16) {
+    case 1: go(std::integral_constant<int, 1>()); break;
+    case 2: go(std::integral_constant<int, 2>()); break;
+    case 3: go(std::integral_constant<int, 3>()); break;
+    case 4: go(std::integral_constant<int, 4>()); break;
+    case 5: go(std::integral_constant<int, 5>()); break;
+    case 6: go(std::integral_constant<int, 6>()); break;
+    case 7: go(std::integral_constant<int, 7>()); break;
+    case 8: go(std::integral_constant<int, 8>()); break;
+    default: return hipErrorInvalidValue;
+  }
+  return hipGetLastError();
+}
+
+// 16-byte loads along a head of q and of the pools
+bool head_vec(int dh, const float* q, int64_t q_ld, const float* kp, int64_t pool_ld) {
+  return dh % 4 == 0 && q_ld % 4 == 0 && pool_ld % 4 == 0 && (uintptr_t)q % 16 == 0 && (uintptr_t)kp % 16 == 0;
 }
 
 }  // namespace
 
 hipError_t launch_gemm_f32(const float* X, const float* W, float* C, int64_t ldc, int M, int N,
                            int K, int accumulate, hipStream_t s) {
+  const int tiles = ((N + TN - 1) / TN) * ((M + TM - 1) / TM);
+  if (tiles <= kSmallTiles && (M + 15) / 16 <= 65535) {
+    const dim3 grid((N + 15) / 16, (M + 15) / 16), block(64 * kSmallWaves);
+    const bool vec = K % 4 == 0 && (uintptr_t)X % 16 == 0 && (uintptr_t)W % 16 == 0;
+    if (vec)
+      hipLaunchKernelGGL(gemm_f32_small_kernel<true>, grid, block, 0, s, X, W, C, ldc, M, N, K, accumulate);
+    else
+      hipLaunchKernelGGL(gemm_f32_small_kernel<false>, grid, block, 0, s, X, W, C, ldc, M, N, K, accumulate);
+    return hipGetLastError();
+  }
   hipLaunchKernelGGL(gemm_f32_kernel, dim3((N + TN - 1) / TN, (M + TM - 1) / TM), dim3(256), 0, s, X,
                      W, C, ldc, M, N, K, accumulate);
   return hipGetLastError();
@@ -292,9 +488,12 @@ hipError_t launch_attention_f32(const Ragged& rg, int H, int Hkv, int dh, const 
   }
   const int rows = rg.cu_rows[rg.batch];
   if (rows == 0) return hipSuccess;
-  hipLaunchKernelGGL(attention_f32_kernel, dim3(rows, H), dim3(64), 0, s, a, H, Hkv, dh, q, read_slots,
-                     k_pool, v_pool, pool_ld, n_slots, out, lse);
-  return hipGetLastError();
+  const int64_t q_ld = (int64_t)H * dh;
+  return by_head_dim(dh, head_vec(dh, q, q_ld, k_pool, pool_ld), [&](auto nd, auto vec) {
+    hipLaunchKernelGGL((attention_f32_kernel<decltype(nd)::value, decltype(vec)::value, false>),
+                       dim3(a.tile_start[a.batch], H), dim3(64 * kAttWaves), 0, s, a, H, Hkv, dh, q, q_ld,
+                       (int64_t)rows, nullptr, read_slots, k_pool, v_pool, pool_ld, n_slots, out, lse);
+  });
 }
 
 hipError_t launch_score_lse_f32(int batch, const int* cu_q, int H, int Hkv, int dh, const float* q,
@@ -303,9 +502,14 @@ hipError_t launch_score_lse_f32(int batch, const int* cu_q, int H, int Hkv, int 
                                 const int32_t* affix_slots, int L, float* lse_out, hipStream_t s) {
   const int n = cu_q[batch];
   if (n == 0) return hipSuccess;
-  hipLaunchKernelGGL(score_lse_f32_kernel, dim3(n, H), dim3(64), 0, s, H, Hkv, dh, q, q_ld, q_n_rows,
-                     q_rows, k_pool, pool_ld, n_slots, affix_slots, L, lse_out);
-  return hipGetLastError();
+  const int all[2] = {0, n};  // every request's queries against the same keys
+  RowsArgs a = rows_args(all, 1);
+  a.key_len[0] = L;
+  return by_head_dim(dh, head_vec(dh, q, q_ld, k_pool, pool_ld), [&](auto nd, auto vec) {
+    hipLaunchKernelGGL((attention_f32_kernel<decltype(nd)::value, decltype(vec)::value, true>),
+                       dim3(a.tile_start[1], H), dim3(64 * kAttWaves), 0, s, a, H, Hkv, dh, q, q_ld, q_n_rows,
+                       q_rows, affix_slots, k_pool, nullptr, pool_ld, n_slots, nullptr, lse_out);
+  });
 }
 
 hipError_t launch_score_colsum_f32(int batch, const int* cu_q, int H, int Hkv, int dh,
@@ -314,10 +518,11 @@ hipError_t launch_score_colsum_f32(int batch, const int* cu_q, int H, int Hkv, i
                                    int64_t n_slots, const int32_t* affix_slots, int L,
                                    const float* lse, int lse_by_qrow, float* part, hipStream_t s) {
   RowsArgs a = rows_args(cu_q, batch);
-  hipLaunchKernelGGL(score_colsum_f32_kernel, dim3((L + 63) / 64, H, batch), dim3(64), 0, s, a, H, Hkv, dh,
-                     q, q_ld, q_n_rows, q_rows, k_pool, pool_ld, n_slots, affix_slots, L, lse, lse_by_qrow,
-                     part);
-  return hipGetLastError();
+  return by_head_dim(dh, head_vec(dh, q, q_ld, k_pool, pool_ld), [&](auto nd, auto vec) {
+    hipLaunchKernelGGL((score_colsum_f32_kernel<decltype(nd)::value, decltype(vec)::value>),
+                       dim3((L + 15) / 16, H, batch), dim3(64 * kAttWaves), 0, s, a, H, Hkv, dh, q, q_ld, q_n_rows,
+                       q_rows, k_pool, pool_ld, n_slots, affix_slots, L, lse, lse_by_qrow, part);
+  });
 }
 
 }  // namespace acache
