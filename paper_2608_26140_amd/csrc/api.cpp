@@ -137,9 +137,10 @@ WsPlan plan_ws(const acache_dims* d, int rows, int batch, int L) {
   if (d->dtype == ACACHE_BF16) {
     // largest splits x rows over every row count up to `rows`, so one
     // workspace serves any smaller call (splits change only at row-tile
-    // boundaries, every one of which is a multiple of 128 rows)
+    // boundaries, every one of which is a multiple of 128 rows; up to
+    // kRowsMax rows the partials fit the stream-K space below)
     size_t part_elems = 0;
-    for (int t = 1; (t - 1) * 128 < rows; ++t) {
+    for (int t = kRowsMax / 128 + 1; (t - 1) * 128 < rows; ++t) {
       const int m = std::min(rows, t * 128);
       const int sp = std::max(gemm_bf16_splits(m, d->d_model, (int)hq), gemm_bf16_splits(m, d->d_model, d->d_ff));
       part_elems = std::max(part_elems, (size_t)sp * (size_t)m * d->d_model);

@@ -38,6 +38,8 @@ hipError_t launch_rmsnorm(acache_dtype dt, const void* x, const void* g, void* y
 // y[m] = RMSNorm(x[m]) * g.
 hipError_t launch_reduce_residual(void* x, const float* part, int splits, int M, int d,
                                   const void* g, void* y, float eps, hipStream_t s);
+// c[m] = sum_s part[s][m] (bf16 c [M, d], d % 8 == 0, d <= 8192)
+hipError_t launch_reduce_store(void* c, const float* part, int splits, int M, int d, hipStream_t s);
 // q[rows[i]] = rotary(sum_s part[s][i], pos[rows[i]]) for the n rows of bf16
 // queries with head_dim 128 (fp32 partials [splits][n][H * 128]).
 // bf16 RMSNorm of gathered rows: y[i] = norm(x[src_rows[i]]) (zero for an
@@ -79,6 +81,12 @@ struct GemmParams {
 };
 hipError_t launch_gemm_bf16(GemmEpi epi, const GemmParams& p, hipStream_t s);
 int gemm_bf16_splits(int M, int N, int K);  // split-K choice for EPI_PARTIAL
+// The kernel for few rows (k_gemm_rows.hip), M <= kRowsMax.  Its partials fit
+// gemm_bf16_sk_ws_bytes(); gemm_rows_us: its estimated time unsplit.
+constexpr int kRowsMax = 256;
+int gemm_rows_splits(int M, int N, int K);
+double gemm_rows_us(int M, int N, int K);
+hipError_t launch_gemm_rows(GemmEpi epi, const GemmParams& p, hipStream_t s);
 size_t gemm_bf16_sk_ws_bytes();             // stream-K workspace (any shape)
 
 hipError_t launch_argmax_commit(acache_dtype dt, const void* x, int64_t ld, int rows, int n, int32_t* out,

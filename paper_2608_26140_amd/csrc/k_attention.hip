@@ -461,36 +461,6 @@ __global__ __launch_bounds__(256) void attention_merge_kernel(const float* __res
 // under 10% faster, so neither is what bounds the loop).
 // ============================================================================
 
-typedef uint32_t rsrc_words __attribute__((ext_vector_type(4)));
-
-// Raw buffer descriptor over [base, base + bytes) in SGPRs (stride 0: loads
-// at or past `bytes` return zeros).
-__device__ __forceinline__ rsrc_words buffer_words(const void* base, uint32_t bytes) {
-  const uint64_t p = (uint64_t)(uintptr_t)base;
-  rsrc_words w;
-  w.x = __builtin_amdgcn_readfirstlane((uint32_t)p);
-  w.y = __builtin_amdgcn_readfirstlane((uint32_t)(p >> 32) & 0xFFFFu);
-  w.z = __builtin_amdgcn_readfirstlane(bytes);
-  w.w = 0x00020000u;
-  return w;
-}
-// 16 bytes per lane, buffer -> LDS at lds + 16 * lane (lds wave-uniform).
-__device__ __forceinline__ void dma16_asm(rsrc_words r, uint32_t voff, const char* lds) {
-  const uint32_t m0 = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)lds);
-  asm volatile("buffer_load_dwordx4 %0, %1, 0 offen lds" ::"v"(voff), "s"(r), "{m0}"(m0) : "memory");
-}
-// 4 bytes per lane, buffer -> LDS at lds + 4 * lane.
-__device__ __forceinline__ void dma4_asm(rsrc_words r, uint32_t voff, const char* lds) {
-  const uint32_t m0 = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)lds);
-  asm volatile("buffer_load_dword %0, %1, 0 offen lds" ::"v"(voff), "s"(r), "{m0}"(m0) : "memory");
-}
-// s_waitcnt vmcnt(N) that the compiler cannot move memory accesses across.
-template <int N>
-__device__ __forceinline__ void wait_vm_asm() {
-  static_assert(N >= 0 && N < 64, "vmcnt field");
-  asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
-}
-
 constexpr int kWdStages = 4;                     // K + V stages in the ring
 constexpr int kWdKAhead = 3;                     // K fragments read ahead, in MFMA chunks
 constexpr int kWdVAhead = 2;                     // V fragments read ahead

@@ -1088,6 +1088,7 @@ hipError_t launch_plan(GemmEpi epi, const GemmParams& p, const Plan& pl, hipStre
 }  // namespace
 
 int gemm_bf16_splits(int M, int N, int K) {
+  if (M <= kRowsMax) return gemm_rows_splits(M, N, K);
   return partial_half(M, N, K) ? splits_for<GemmCfgH>(M, N, K, nullptr) : splits_for<GemmCfg>(M, N, K, nullptr);
 }
 
@@ -1099,9 +1100,19 @@ size_t gemm_bf16_sk_ws_bytes() {
 hipError_t launch_gemm_bf16(GemmEpi epi, const GemmParams& p, hipStream_t s) {
   bool half;
   if (epi == EPI_PARTIAL) {
+    if (p.M <= kRowsMax) return launch_gemm_rows(epi, p, s);
     half = partial_half(p.M, p.N, p.K);
   } else {
-    half = plan_cfg<GemmCfgH>(epi, p).cost < plan_cfg<GemmCfg>(epi, p).cost;
+    const double c256 = plan_cfg<GemmCfg>(epi, p).cost, c128 = plan_cfg<GemmCfgH>(epi, p).cost;
+    half = c128 < c256;
+    // Few rows: the kernel made for them, unless these tiles come out ahead,
+    // at 1.4 (1.9) us per K step of 256 x 256 (256 x 128) tiles and 4 TB/s of
+    // weights.  256 rows: 37,888 x 3584 88 us here and 110 there, 24,576 x 4096
+    // 90 and 64, 12,288 x 4096 82 and 58.
+    const double tiles_us = std::max(std::min(1.4 * c256, 1.9 * c128), (double)p.N * p.K * 2.0 / 4e6) + 12.0;
+    const bool narrow = p.N <= 8192 && p.sk_ws && (epi == EPI_STORE || epi == EPI_ACCUM);  // takes K splits there
+    if (p.M <= kRowsMax && (p.M <= 128 || narrow || gemm_rows_us(p.M, p.N, p.K) < tiles_us))
+      return launch_gemm_rows(epi, p, s);
   }
   return half ? launch_plan<GemmCfgH>(epi, p, plan_cfg<GemmCfgH>(epi, p), s)
               : launch_plan<GemmCfg>(epi, p, plan_cfg<GemmCfg>(epi, p), s);

@@ -247,8 +247,8 @@ __global__ __launch_bounds__(256) void q_rotary_reduce_kernel(const float* __res
 // Chunk c of thread t is column chunk t + 256 c; the loads are issued for
 // all NC chunks of a split (clamped to the last chunk, results of absent
 // chunks unused) so that they are in flight together.  Each element is
-// x + p_0 + p_1 + ... in split order.
-template <int NC>
+// x + p_0 + p_1 + ... in split order; FRESH: p_0 + p_1 + ..., x not read.
+template <int NC, bool FRESH = false>
 __global__ __launch_bounds__(256) void reduce_residual_kernel(bf16* __restrict__ x, const float* __restrict__ part,
                                                               int splits, int M, int d,
                                                               const bf16* __restrict__ g,
@@ -263,7 +263,8 @@ __global__ __launch_bounds__(256) void reduce_residual_kernel(bf16* __restrict__
     const int ch = threadIdx.x + c * 256;
     ok[c] = ch < nch;
     off[c] = row * d + (int64_t)min(ch, nch - 1) * 8;
-    const bf16x8 xv = *reinterpret_cast<const bf16x8*>(x + off[c]);
+    bf16x8 xv = {};
+    if constexpr (!FRESH) xv = *reinterpret_cast<const bf16x8*>(x + off[c]);
 #pragma unroll
     for (int j = 0; j < 8; ++j) v[c][j] = (float)xv[j];
   }
@@ -698,6 +699,18 @@ hipError_t launch_reduce_residual(void* x, const float* part, int splits, int M,
   else if (nc == 2) go(reduce_residual_kernel<2>);
   else if (nc == 3) go(reduce_residual_kernel<3>);
   else go(reduce_residual_kernel<4>);
+  return hipGetLastError();
+}
+
+hipError_t launch_reduce_store(void* c, const float* part, int splits, int M, int d, hipStream_t s) {
+  const int nc = ((d >> 3) + 255) / 256;
+  auto go = [&](auto kern) {
+    hipLaunchKernelGGL(kern, dim3(M), dim3(256), 0, s, (bf16*)c, part, splits, M, d, nullptr, nullptr, 0.f);
+  };
+  if (nc <= 1) go(reduce_residual_kernel<1, true>);
+  else if (nc == 2) go(reduce_residual_kernel<2, true>);
+  else if (nc == 3) go(reduce_residual_kernel<3, true>);
+  else go(reduce_residual_kernel<4, true>);
   return hipGetLastError();
 }
 

@@ -115,3 +115,94 @@ def test_attention_and_scores_f32_edges(A, H, Hkv, dh):
         A.acache_score(dims, qa, up_i32(q_rows), cu_q, pools[0], up_i32(aff), scores)
         ref = O.scores_via_slots(f(q).reshape(-1, H, dh), q_rows, cu_q, kz[:-1], aff, "affix", None)
         assert_close(down(scores), ref, "f32", "scores")
+
+
+# ----------------------------------------------------------------------------- bf16 products of few rows
+
+@pytest.mark.parametrize("M", [1, 16, 31, 33, 64, 65, 96, 97, 128, 129, 192, 193, 256, 257])
+@pytest.mark.parametrize("N,K,acc", [
+    (256, 64, 0),       # one K step
+    (768, 192, 1),      # fewer K steps than the ring holds
+    (4608, 512, 0),     # narrow: split along K where a workspace is given
+    (8448, 320, 1),     # wider than the split path takes, a last workgroup that is part full
+    (12288, 2048, 0),   # staggered K starts
+    (33280, 128, 1),    # more tiles than CUs: workgroups take several
+])
+def test_linear_few_rows(A, M, N, K, acc):
+    """Both sides of every row bucket and of the last row count of the kernel
+    for few rows; with and without a workspace (K splits)."""
+    import torch
+    a = W.draw_tensor((M, K), "bf16", seed=M)
+    w = W.draw_tensor((N, K), "bf16", std=0.05, seed=N + K)
+    c0 = W.draw_tensor((M, N), "bf16", seed=7)
+    dims = A.make_dims(4096, 32, 32, 128, 256, "bf16")
+    ws = A.workspace(dims, M, 1, 0)
+    da, dw = up(a, "bf16"), up(w, "bf16")
+    # the oracle's product, in fp64 on the device: the same bits as inputs
+    ref = da.double() @ dw.double().t() + (up(c0, "bf16").double() if acc else 0.0)
+    got = []
+    for work in (None, ws):
+        c = up(c0, "bf16").clone()
+        A.acache_linear(dims, da, dw, out=c, accumulate=bool(acc), ws=work)
+        assert_close(down(c), ref.cpu().numpy(), "bf16", f"linear {M}x{N}x{K} ws {work is not None}")
+        again = up(c0, "bf16").clone()
+        A.acache_linear(dims, da, dw, out=again, accumulate=bool(acc), ws=work)
+        assert torch.equal(c, again)  # sums in a fixed order
+        got.append(c)
+
+
+@pytest.mark.parametrize("B,blk", [(1, 16), (1, 32), (2, 32), (3, 32), (4, 33), (5, 32), (8, 32), (7, 37)])
+@pytest.mark.parametrize("H,Hkv,F,d", [(4, 4, 1024, 512), (6, 2, 896, 768)])
+def test_layer_few_rows(A, B, blk, H, Hkv, F, d):
+    """acache_layer_recompute at row counts on both sides of the few-row
+    kernel's buckets (16 .. 259 rows): the rotary, K/V store, SwiGLU and
+    split-K epilogues, against the oracle's block in fp64; some rows have no
+    valid write slot (nothing stored)."""
+    import torch
+    rng = np.random.default_rng(B * blk + H)
+    dh, M, S = 128, B * blk, blk + 40
+    shapes = dict(w_qkv=((H + 2 * Hkv) * dh, d), w_o=(d, H * dh), w_gate_up=(2 * F, d), w_down=(d, F))
+    bits = {n: W.draw_tensor(s, "bf16", std=0.04, seed=i) for i, (n, s) in enumerate(shapes.items())}
+    bits["attn_norm"] = bits["mlp_norm"] = W.draw_tensor((d,), "bf16", seed=9)
+    x0 = W.draw_tensor((M, d), "bf16", seed=10)
+    n_slots = B * S + 3
+    kp, vp = (W.draw_tensor((n_slots, Hkv * dh), "bf16", seed=11 + i) for i in range(2))
+    read = rng.permutation(n_slots)[:B * S].reshape(B, S)
+    write = read[:, 40:].copy()
+    pos = rng.integers(0, 9000, size=(B, blk))
+    bad = write.reshape(-1).copy()
+    bad[M // 2] = n_slots + 5  # dropped; its key keeps the pool's row
+    dims = A.make_dims(d, H, Hkv, dh, F, "bf16")
+    dev = {n: up(b, "bf16") for n, b in bits.items()}
+    x, gk, gv = up(x0, "bf16").clone(), up(kp, "bf16").clone(), up(vp, "bf16").clone()
+    ws = A.workspace(dims, M, B, 0)
+    A.acache_layer_recompute(dims, dev, [b * blk for b in range(B + 1)], [b * S for b in range(B + 1)], x,
+                             up_i32(pos.reshape(-1)), up_i32(bad), up_i32(read.reshape(-1)), gk, gv, ws)
+    # the same block in fp64 with plain torch operations
+    D = lambda t: t.double()  # noqa: E731
+    norm = lambda t, g: t / torch.sqrt((t * t).mean(1, keepdim=True) + 1e-5) * D(g)  # noqa: E731
+    xr = D(up(x0, "bf16"))
+    y = norm(xr, dev["attn_norm"])
+    qkv = (y @ D(dev["w_qkv"]).t()).view(M, H + 2 * Hkv, dh)
+    th = 10000.0 ** (-2.0 * torch.arange(64, device="cuda", dtype=torch.float64) / dh)
+    an = torch.from_numpy(pos.reshape(-1)).cuda().double()[:, None, None] * th
+    rot = torch.cat([qkv[..., :64] * an.cos() - qkv[..., 64:] * an.sin(),
+                     qkv[..., 64:] * an.cos() + qkv[..., :64] * an.sin()], 2)
+    K, V = D(up(kp, "bf16")), D(up(vp, "bf16"))
+    ok = torch.from_numpy(bad < n_slots).cuda()
+    wsl = torch.from_numpy(bad).cuda().long()[ok]
+    K[wsl] = rot[:, H:H + Hkv].reshape(M, -1)[ok]
+    V[wsl] = qkv[:, H + Hkv:].reshape(M, -1)[ok]
+    assert_close(down(gk), K.cpu().numpy(), "bf16", "K pool")
+    assert_close(down(gv), V.cpu().numpy(), "bf16", "V pool")
+    o = torch.zeros(M, H * dh, dtype=torch.float64, device="cuda")
+    for b in range(B):
+        sl = torch.from_numpy(read[b]).cuda().long()
+        for h in range(H):
+            g = slice(h // (H // Hkv) * dh, (h // (H // Hkv) + 1) * dh)
+            lg = rot[b * blk:(b + 1) * blk, h] @ K[sl][:, g].t() / np.sqrt(dh)
+            o[b * blk:(b + 1) * blk, h * dh:(h + 1) * dh] = torch.softmax(lg, 1) @ V[sl][:, g]
+    xr = xr + o @ D(dev["w_o"]).t()
+    gu = norm(xr, dev["mlp_norm"]) @ D(dev["w_gate_up"]).t()
+    xr = xr + (torch.nn.functional.silu(gu[:, :F]) * gu[:, F:]) @ D(dev["w_down"]).t()
+    assert_close(down(x), xr.cpu().numpy(), "bf16", "layer rows")
