@@ -107,13 +107,7 @@ struct PvArgs {
   // with lse_aff and splits > 1: [splits][rows][H], each split's log-sum-exp
   // (log2 units) over its tiles below aff_t1, -inf for a split past them
   float* part_aff;
-  // decode passes: both write partials into one buffer of part_rows rows,
-  // this launch's splits at indices split_base ..
-  int partial;
-  int split_base;
-  int64_t part_rows;
-  // MASK kernels: bit i of key_mask[(row / mask_rows) * mask_tiles + t] drops
-  // key 64 t + i for that query row
+  // masked attention_wide_kernel: [requests][mask_tiles] words, mask_rows rows a request
   const uint64_t* key_mask;
   int mask_tiles;
   int mask_rows;
@@ -123,68 +117,30 @@ __device__ __forceinline__ v4i16 ds_read_tr16(const char* lds) {
   return __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) v4i16*)lds);
 }
 
+struct PvPool {
+  const bf16* k_pool;
+  const bf16* v_pool;
+  int64_t pool_ld;
+  int64_t n_slots;
+};
+
+// Key tiles [t_lo, t_hi) of one request for the 32 queries of each wavefront
+// (qf: this lane's query, lane % 32), KV head g: O^T, the running maximum
+// (log2 units), this lane half's share of the sum, and the log-sum-exp after
+// tile aff_t1 - 1.  MASK: bit i of mrow[t] drops key 64 t + i for this lane's
+// query (null: none); one_mask: the wavefront's queries share it.  A wavefront
+// that is not live only copies and synchronises.
 template <bool MASK>
-__global__ __launch_bounds__(kPvThreads, 2) void attention_pv_kernel(PvArgs pa) {
-  __shared__ __attribute__((aligned(1024))) char ring[2 * kStageB];
-  const AttnArgs& a = pa.a;
-  const int splits = pa.splits;
-
-  // XCD-contiguous, head-major order of (head, query tile, key split)
-  const int n_tiles_q = a.tile_start[a.batch];
-  int h, tile, split;
-  {
-    const int nb = gridDim.x, i = blockIdx.x;
-    const int q8 = nb >> 3, r8 = nb & 7, x = i & 7;
-    const int t = x * q8 + min(x, r8) + (i >> 3);
-    h = t / (n_tiles_q * splits);
-    const int rem = t - h * n_tiles_q * splits;
-    tile = rem / splits;
-    split = rem - tile * splits;
-  }
-  int b = 0;
-  {
-    int lo = 0, hi = a.batch - 1;
-    while (lo < hi) {
-      const int mid = (lo + hi + 1) >> 1;
-      if (a.tile_start[mid] <= tile) lo = mid; else hi = mid - 1;
-    }
-    b = lo;
-  }
-  const int g = h / (a.H / a.Hkv);
+__device__ __forceinline__ void pv_tiles(const PvPool& kv, char* ring, const int32_t* slots, int S, int t_lo,
+                                         int t_hi, int g, bool live, const bf16x8 (&qf)[8], const uint64_t* mrow,
+                                         bool one_mask, int aff_t1, f32x16 (&o_acc)[4], float& m_run, float& l_part,
+                                         float& lse_aff2) {
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, hl = lane >> 5;
-  const int n_rows = a.row_n[b];
-  const int64_t r0 = (int64_t)a.row_start[b] + a.row_lo[b];  // global row of query 0
-  const int qi = (tile - a.tile_start[b]) * kPvTileQ + wave * 32 + (lane & 31);
-  const bool q_ok = qi < n_rows;
-  // a wavefront without a valid query only copies and synchronises
-  const bool live = __builtin_amdgcn_ballot_w64(q_ok) != 0;
-  const int S = a.key_len[b];
-  const int32_t* slots = a.slots + a.key_start[b];
-  const int n_kt = (S + kTileK - 1) / kTileK;
-  const int t_lo = split * n_kt / splits, t_hi = (split + 1) * n_kt / splits;
-
-  bf16x8 qf[8];
-  {
-    int64_t qrow = q_ok ? r0 + qi : -1;
-    const bf16* qp = a.q + (qrow < 0 ? 0 : qrow) * a.q_ld + h * kDh + hl * 8;
-#pragma unroll
-    for (int s2 = 0; s2 < 8; ++s2) {
-      u32x4 v = {0u, 0u, 0u, 0u};
-      if (qrow >= 0) v = *reinterpret_cast<const u32x4*>(qp + s2 * 16);
-      qf[s2] = __builtin_bit_cast(bf16x8, v);
-    }
-  }
-
-  const uint64_t* mrow = nullptr;  // this query row's key mask (MASK)
-  if constexpr (MASK) {
-    if (q_ok) mrow = pa.key_mask + (int64_t)((r0 + qi) / pa.mask_rows) * pa.mask_tiles;
-  }
-
   // this lane's 4 keys of a tile (one per load): key 16 wave + 4 i + lane / 16,
   // 16-byte chunk position lane % 16
   const int pch = lane & 15;
   const uint32_t head_b = (uint32_t)g * kRowB;
-  const uint32_t ld_b = (uint32_t)a.pool_ld * 2u;
+  const uint32_t ld_b = (uint32_t)kv.pool_ld * 2u;
   int slot_next[kDmaPerTile];   // slots of the tile to issue next
   unsigned absent_bits = 0;     // bit i: this lane's key i of the in-flight tile is absent
   auto key_of = [&](int t, int i) { return t * kTileK + wave * 16 + 4 * i + (lane >> 4); };
@@ -199,14 +155,14 @@ __global__ __launch_bounds__(kPvThreads, 2) void attention_pv_kernel(PvArgs pa) 
     for (int i = 0; i < kDmaPerTile; ++i) {
       const int key = key_of(t, i);
       const int sl = slot_next[i];
-      const bool ok = key < S && sl >= 0 && sl < a.n_slots;
+      const bool ok = key < S && sl >= 0 && sl < kv.n_slots;
       ab |= (ok ? 0u : 1u) << i;
       const uint32_t base = (ok ? (uint32_t)sl : 0u) * ld_b + head_b;
       const int r = key & (kTileK - 1);
       const int ck = pch ^ (r & 15), cv = pch ^ ((r & 3) << 1);
       const int dst = (wave * kDmaPerTile + i) * 1024;
-      dma16((const char*)a.k_pool + base + ck * 16, st + dst);
-      dma16((const char*)a.v_pool + base + cv * 16, st + kTileB + dst);
+      dma16((const char*)kv.k_pool + base + ck * 16, st + dst);
+      dma16((const char*)kv.v_pool + base + cv * 16, st + kTileB + dst);
     }
     absent_bits = ab;
   };
@@ -225,14 +181,15 @@ __global__ __launch_bounds__(kPvThreads, 2) void attention_pv_kernel(PvArgs pa) 
     }
   };
 
-  f32x16 o_acc[4];
 #pragma unroll
   for (int d = 0; d < 4; ++d)
 #pragma unroll
     for (int r = 0; r < 16; ++r) o_acc[d][r] = 0.f;
-  float m_run = -INFINITY, l_part = 0.f, lse_aff2 = -INFINITY;
+  m_run = -INFINITY;
+  l_part = 0.f;
+  lse_aff2 = -INFINITY;
   // the affix tiles of this split end before tile aff_end (none if past them)
-  const int aff_end = min(a.aff_t1, t_hi);
+  const int aff_end = min(aff_t1, t_hi);
   const float scale = kLog2e * rsqrtf((float)kDh);
   const int krow = key_perm(lane & 31);
   // K fragment byte offsets inside a tile for key block 0 (block 1: + 32 rows)
@@ -279,7 +236,22 @@ __global__ __launch_bounds__(kPvThreads, 2) void attention_pv_kernel(PvArgs pa) 
     uint64_t drop = kt0 + kTileK <= S ? 0ull : ~0ull << (S - kt0);
     if constexpr (MASK) drop |= mrow ? mrow[t] : 0ull;
     float mx = -INFINITY;
-    if (drop == 0ull) {
+    if (MASK && one_mask) {
+      // all the wave's queries drop the same keys: lane masks made of two
+      // scalar bits each, one select per logit
+      const uint32_t d2[2] = {(uint32_t)__builtin_amdgcn_readfirstlane((int)drop),
+                              (uint32_t)__builtin_amdgcn_readfirstlane((int)(drop >> 32))};
+#pragma unroll
+      for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+          const int bit = 16 * (r >> 3) + (r & 7);
+          const uint32_t lo = (d2[kb] >> bit) & 1u ? ~0u : 0u, hi = (d2[kb] >> (bit + 8)) & 1u ? ~0u : 0u;
+          const bool out = __builtin_amdgcn_inverse_ballot_w64((uint64_t)hi << 32 | lo);
+          st[kb][r] = out ? -INFINITY : st[kb][r];
+          mx = fmaxf(mx, st[kb][r]);
+        }
+    } else if (drop == 0ull) {
 #pragma unroll
       for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
@@ -340,15 +312,71 @@ __global__ __launch_bounds__(kPvThreads, 2) void attention_pv_kernel(PvArgs pa) 
         }
       }
   }
+}
+
+__global__ __launch_bounds__(kPvThreads, 2) void attention_pv_kernel(PvArgs pa) {
+  __shared__ __attribute__((aligned(1024))) char ring[2 * kStageB];
+  const AttnArgs& a = pa.a;
+  const int splits = pa.splits;
+
+  // XCD-contiguous, head-major order of (head, query tile, key split)
+  const int n_tiles_q = a.tile_start[a.batch];
+  int h, tile, split;
+  {
+    const int nb = gridDim.x, i = blockIdx.x;
+    const int q8 = nb >> 3, r8 = nb & 7, x = i & 7;
+    const int t = x * q8 + min(x, r8) + (i >> 3);
+    h = t / (n_tiles_q * splits);
+    const int rem = t - h * n_tiles_q * splits;
+    tile = rem / splits;
+    split = rem - tile * splits;
+  }
+  int b = 0;
+  {
+    int lo = 0, hi = a.batch - 1;
+    while (lo < hi) {
+      const int mid = (lo + hi + 1) >> 1;
+      if (a.tile_start[mid] <= tile) lo = mid; else hi = mid - 1;
+    }
+    b = lo;
+  }
+  const int g = h / (a.H / a.Hkv);
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, hl = lane >> 5;
+  const int n_rows = a.row_n[b];
+  const int64_t r0 = (int64_t)a.row_start[b] + a.row_lo[b];  // global row of query 0
+  const int qi = (tile - a.tile_start[b]) * kPvTileQ + wave * 32 + (lane & 31);
+  const bool q_ok = qi < n_rows;
+  // a wavefront without a valid query only copies and synchronises
+  const bool live = __builtin_amdgcn_ballot_w64(q_ok) != 0;
+  const int S = a.key_len[b];
+  const int32_t* slots = a.slots + a.key_start[b];
+  const int n_kt = (S + kTileK - 1) / kTileK;
+  const int t_lo = split * n_kt / splits, t_hi = (split + 1) * n_kt / splits;
+
+  bf16x8 qf[8];
+  {
+    int64_t qrow = q_ok ? r0 + qi : -1;
+    const bf16* qp = a.q + (qrow < 0 ? 0 : qrow) * a.q_ld + h * kDh + hl * 8;
+#pragma unroll
+    for (int s2 = 0; s2 < 8; ++s2) {
+      u32x4 v = {0u, 0u, 0u, 0u};
+      if (qrow >= 0) v = *reinterpret_cast<const u32x4*>(qp + s2 * 16);
+      qf[s2] = __builtin_bit_cast(bf16x8, v);
+    }
+  }
+
+  f32x16 o_acc[4];
+  float m_run, l_part, lse_aff2;
+  pv_tiles<false>({a.k_pool, a.v_pool, a.pool_ld, a.n_slots}, ring, slots, S, t_lo, t_hi, g, live, qf, nullptr, false,
+                  a.aff_t1, o_acc, m_run, l_part, lse_aff2);
 
   const float l_tot = l_part + __shfl_xor(l_part, 32);
   if (!q_ok) return;
   const int64_t row = r0 + qi;
-  if (splits > 1 || pa.partial) {
+  if (splits > 1) {
     // unnormalised partial: O^T register r of block d holds dims 32 d + 8 (r / 4) + 4 hl + r % 4
-    const int64_t prow = pa.partial ? pa.part_rows : (int64_t)a.row_start[a.batch];
-    const int psplit = pa.split_base + split;
-    float* po = pa.part_o + (((int64_t)psplit * prow + row) * a.H + h) * kDh;
+    const int64_t prow = (int64_t)a.row_start[a.batch];
+    float* po = pa.part_o + (((int64_t)split * prow + row) * a.H + h) * kDh;
 #pragma unroll
     for (int d = 0; d < 4; ++d)
 #pragma unroll
@@ -357,10 +385,10 @@ __global__ __launch_bounds__(kPvThreads, 2) void attention_pv_kernel(PvArgs pa) 
         *reinterpret_cast<f32x4*>(po + d * 32 + 8 * gq + 4 * hl) = v;
       }
     if (hl == 0) {
-      float* pm = pa.part_ml + (((int64_t)psplit * prow + row) * a.H + h) * 2;
+      float* pm = pa.part_ml + (((int64_t)split * prow + row) * a.H + h) * 2;
       pm[0] = m_run;
       pm[1] = l_tot;
-      if (pa.part_aff) pa.part_aff[((int64_t)psplit * prow + row) * a.H + h] = lse_aff2;
+      if (pa.part_aff) pa.part_aff[((int64_t)split * prow + row) * a.H + h] = lse_aff2;
     }
     return;
   }
@@ -377,6 +405,100 @@ __global__ __launch_bounds__(kPvThreads, 2) void attention_pv_kernel(PvArgs pa) 
       for (int j = 0; j < 4; ++j) w[j] = (bf16)(o_acc[d][4 * gq + j] * inv);
       *reinterpret_cast<bf16x4*>(op + d * 32 + 8 * gq + 4 * hl) = w;
     }
+}
+
+// ============================================================================
+// Decode-step attention: a view made of the shared affix (minus each request's
+// anchors) and each request's private keys.  Shared workgroups take the
+// queries of all requests against a range of the affix keys, so each affix
+// tile is read once per 128 queries; private ones take one request's queries
+// against a range of its own keys.  A workgroup's time is its chain of tiles
+// (load, logits, softmax, product: 2-3 us each at two workgroups per CU), so
+// both kinds are split along their keys until the CUs are full, and share one
+// launch; with grouped heads the query heads of a KV head are taken as further
+// rows of the tile.  All write (O, max, sum) partials for
+// attention_merge_kernel.  Measured with the merge, before = two launches,
+// the private one unsplit: 1 x 32 rows, 32 heads, 1024 + 717 keys 50 -> 30 us;
+// 4 x 32 rows, 28 heads on 4, 4096 + 1843 keys 91 -> 48 us.
+// Large batches take the shared affix on attention_wide_kernel instead, ahead
+// of a launch with the private workgroups alone, which HBM bounds.
+// ============================================================================
+struct DecArgs {
+  PvPool kv;
+  const bf16* q;               // [rows, H * 128]
+  const int32_t* affix_slots;  // [L]
+  const uint64_t* mask;        // [batch][ceil(L / 64)]: bit set for request b's anchors
+  const int32_t* private_slots;
+  float* part_o;   // [sp_shared + sp_private][rows][H][128]
+  float* part_ml;  // [..][rows][H][2]
+  int L, private_len;
+  int H, Hkv;
+  int rows, rows_per_req;
+  int n_shared, n_private;    // workgroups
+  int sp_shared, sp_private;  // key splits
+  int tiles_shared, tiles_private;  // query tiles per KV head (and request)
+};
+
+__global__ __launch_bounds__(kPvThreads, 2) void attention_decode_kernel(DecArgs a) {
+  __shared__ __attribute__((aligned(1024))) char ring[2 * kStageB];
+  // XCD-contiguous order, the two kinds dealt in turn
+  const int nb = gridDim.x, i = blockIdx.x;
+  const int q8 = nb >> 3, r8 = nb & 7, x = i & 7;
+  const int t = x * q8 + min(x, r8) + (i >> 3);
+  const int before = (int)((int64_t)t * a.n_shared / nb);
+  const bool shared = (int)((int64_t)(t + 1) * a.n_shared / nb) > before;
+  int u = shared ? before : t - before;  // request, KV head, query tile, split
+  const int splits = shared ? a.sp_shared : a.sp_private, tiles = shared ? a.tiles_shared : a.tiles_private;
+  const int split = u % splits;
+  u /= splits;
+  const int tile = u % tiles;
+  u /= tiles;
+  const int g = u % a.Hkv, b = u / a.Hkv;  // b: 0 for shared workgroups
+  const int rep = a.H / a.Hkv;
+  const int nr = shared ? a.rows : a.rows_per_req;  // rows; a tile's queries are (head of g, row)
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, hl = lane >> 5;
+  const int v = tile * kPvTileQ + wave * 32 + (lane & 31);
+  const bool q_ok = v < nr * rep;
+  const int h = g * rep + (q_ok ? v / nr : 0);
+  const int row = b * a.rows_per_req + (q_ok ? v % nr : 0);
+  const bool live = __builtin_amdgcn_ballot_w64(q_ok) != 0;
+
+  bf16x8 qf[8];
+  const bf16* qp = a.q + (int64_t)row * a.H * kDh + h * kDh + hl * 8;
+#pragma unroll
+  for (int s2 = 0; s2 < 8; ++s2) {
+    u32x4 w = {0u, 0u, 0u, 0u};
+    if (q_ok) w = *reinterpret_cast<const u32x4*>(qp + s2 * 16);
+    qf[s2] = __builtin_bit_cast(bf16x8, w);
+  }
+  const int S = shared ? a.L : a.private_len;
+  const int n_kt = (S + kTileK - 1) / kTileK;
+  const int t_lo = (int)((int64_t)split * n_kt / splits), t_hi = (int)((int64_t)(split + 1) * n_kt / splits);
+  const int64_t pair = ((int64_t)((shared ? 0 : a.sp_shared) + split) * a.rows + row) * a.H + h;
+  float* po = a.part_o + pair * kDh;
+  const int req = row / a.rows_per_req;
+  const uint64_t* mrow = shared ? a.mask + (int64_t)req * n_kt : nullptr;
+  // lanes without a query take the first lane's mask
+  const int req0 = __builtin_amdgcn_readfirstlane(req);
+  const bool one_mask = shared && __builtin_amdgcn_ballot_w64(q_ok && req != req0) == 0;
+  if (one_mask) mrow = a.mask + (int64_t)req0 * n_kt;
+  f32x16 o_acc[4];
+  float m_run, l_part, lse_aff2;
+  pv_tiles<true>(a.kv, ring, shared ? a.affix_slots : a.private_slots + (int64_t)b * a.private_len, S, t_lo, t_hi, g,
+                 live, qf, mrow, one_mask, 0, o_acc, m_run, l_part, lse_aff2);
+  const float l_tot = l_part + __shfl_xor(l_part, 32);
+  if (!q_ok) return;
+#pragma unroll
+  for (int d = 0; d < 4; ++d)
+#pragma unroll
+    for (int gq = 0; gq < 4; ++gq) {
+      const f32x4 w = {o_acc[d][4 * gq], o_acc[d][4 * gq + 1], o_acc[d][4 * gq + 2], o_acc[d][4 * gq + 3]};
+      *reinterpret_cast<f32x4*>(po + d * 32 + 8 * gq + 4 * hl) = w;
+    }
+  if (hl == 0) {
+    a.part_ml[pair * 2] = m_run;
+    a.part_ml[pair * 2 + 1] = l_tot;
+  }
 }
 
 // Combines the key splits of each (row, head): m = max_s m_s,
@@ -465,6 +587,7 @@ constexpr int kWdStages = 4;                     // K + V stages in the ring
 constexpr int kWdKAhead = 3;                     // K fragments read ahead, in MFMA chunks
 constexpr int kWdVAhead = 2;                     // V fragments read ahead
 constexpr int kWdSlotB = kTileK * 4;             // one tile's slot indices
+constexpr int kWdMaskTiles = 256;                // key tiles of a masked launch's split, at most
 // buffer offset of an absent key: past every pool the launcher admits
 // (n_slots * pool_ld * 2 <= kWdAbsent), so its loads return zeros
 constexpr uint32_t kWdAbsent = 0xF0000000u;
@@ -481,12 +604,16 @@ struct WideCfg {
   static_assert(kDma * WAVES * 1024 == kTileB && kKeysPerWave == 4 * kDma, "copy split");
 };
 
-template <int QB, int WAVES>
+// MASK: bit i of word t of its request's row of key_mask drops key 64 t + i of
+// a wavefront's queries, which all belong to one request (the decode step's
+// anchors); partials are written whatever the splits.
+template <int QB, int WAVES, bool MASK>
 __global__ __launch_bounds__(64 * WAVES, 1) void attention_wide_kernel(PvArgs pa) {
   using C = WideCfg<QB, WAVES>;
 
   __shared__ __attribute__((aligned(1024))) char ring[kWdStages * kStageB];
   __shared__ __attribute__((aligned(16))) char slot_ring[WAVES * 4 * kWdSlotB];
+  __shared__ uint64_t mask_lds[MASK ? WAVES * kWdMaskTiles : 1];
   const AttnArgs& a = pa.a;
   const int splits = pa.splits;
 
@@ -592,6 +719,31 @@ __global__ __launch_bounds__(64 * WAVES, 1) void attention_wide_kernel(PvArgs pa
   const int v_byte = (gi & 1) * 8;
   const int v_sw = (gi >> 2) << 1;
 
+  uint64_t* const my_mask = mask_lds + (MASK ? wave * kWdMaskTiles : 0);
+  if constexpr (MASK) {
+    // the request of the wavefront's queries (a wavefront past the rows loads row 0's)
+    const int64_t req = (r0 + (live ? q0 : 0)) / pa.mask_rows;
+    for (int i = lane; i < t_hi - t_lo; i += 64) my_mask[i] = pa.key_mask[req * pa.mask_tiles + t_lo + i];
+  }
+  // the logits 2 i and 2 i + 1 (of 16 per key block) of tile t: -inf where masked
+  auto drop_pair = [&](uint64_t w, f32x16 (&st)[QB][2], int i) {
+    const int kb = i >> 3;
+    const uint32_t d = kb ? (uint32_t)(w >> 32) : (uint32_t)w;
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+      const int r = 2 * (i & 7) + u, bit = 16 * (r >> 3) + (r & 7);
+      const uint32_t lo = (d >> bit) & 1u ? ~0u : 0u, hi = (d >> (bit + 8)) & 1u ? ~0u : 0u;
+      const bool out = __builtin_amdgcn_inverse_ballot_w64((uint64_t)hi << 32 | lo);
+#pragma unroll
+      for (int qb = 0; qb < QB; ++qb) st[qb][kb][r] = out ? -INFINITY : st[qb][kb][r];
+    }
+  };
+  auto uniform = [&](uint64_t w) {
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)w);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(w >> 32));
+    return (uint64_t)hi << 32 | lo;
+  };
+
   // S^T of tile t for both query blocks: st[qb][kb], register r of key block
   // kb holding key 32 kb + 16 (r / 8) + 8 hl + r % 8 of the tile
   auto scores = [&](int t, f32x16 (&st)[QB][2]) {
@@ -693,6 +845,11 @@ __global__ __launch_bounds__(64 * WAVES, 1) void attention_wide_kernel(PvArgs pa
     bare_barrier();
     if (live) {
       scores(t_lo, st_a);
+      if constexpr (MASK) {
+        const uint64_t w = uniform(my_mask[0]);
+#pragma unroll
+        for (int i = 0; i < 16; ++i) drop_pair(w, st_a, i);
+      }
       row_max(t_lo, st_a, mx);
       rescale(mx);
     }
@@ -728,10 +885,15 @@ __global__ __launch_bounds__(64 * WAVES, 1) void attention_wide_kernel(PvArgs pa
       const v4i16 hi = ds_read_tr16(vs + (row0 + 4) * kRowB + off);
       return __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
     };
+    uint64_t next_mask = 0;
+    if constexpr (MASK) next_mask = my_mask[min(t + 1, t_hi - 1) - t_lo];
     bf16x8 pb[QB][2][2];
-    float psum[QB];
+    float psum[QB], m_use[QB];
 #pragma unroll
     for (int qb = 0; qb < QB; ++qb) {
+      // with masks a query may not have met a key yet: exponentiate against 0
+      // then, which gives zeros
+      m_use[qb] = MASK && m_run[qb] == -INFINITY ? 0.f : m_run[qb];
       psum[qb] = 0.f;
 #pragma unroll
       for (int kb = 0; kb < 2; ++kb)
@@ -762,7 +924,7 @@ __global__ __launch_bounds__(64 * WAVES, 1) void attention_wide_kernel(PvArgs pa
 #pragma unroll
         for (int u = 0; u < 2; ++u) {
           const int e = 2 * i + u, ekb = e >> 4, r = e & 15;
-          const float x = __builtin_amdgcn_exp2f(fmaf(cur[qb][ekb][r], scale, -m_run[qb]));
+          const float x = __builtin_amdgcn_exp2f(fmaf(cur[qb][ekb][r], scale, -m_use[qb]));
           psum[qb] += x;
           pb[qb][ekb][r >> 3][r & 7] = (bf16)x;
         }
@@ -776,12 +938,14 @@ __global__ __launch_bounds__(64 * WAVES, 1) void attention_wide_kernel(PvArgs pa
       if (t + 1 == aff_end) lse_aff2[qb] = m_run[qb] + __log2f(l_part[qb] + __shfl_xor(l_part[qb], 32));
       mx[qb] = -INFINITY;
     }
+    if constexpr (MASK) next_mask = uniform(next_mask);
 #pragma unroll
     for (int i = 0; i < 16; ++i) {
       if (i + kWdVAhead < 16) vf[(i + kWdVAhead) % (kWdVAhead + 1)] = vfrag(i + kWdVAhead);
       const int kb = i >> 3, g2 = (i >> 2) & 1, d = i & 3;
 #pragma unroll
       for (int qb = 0; qb < QB; ++qb) o_acc[qb][d] = mfma32x32x16(vf[i % (kWdVAhead + 1)], pb[qb][kb][g2], o_acc[qb][d]);
+      if constexpr (MASK) drop_pair(next_mask, nxt, i);
 #pragma unroll
       for (int qb = 0; qb < QB; ++qb) {
         mx[qb] = fmaxf(mx[qb], fmaxf(nxt[qb][i >> 3][2 * (i & 7)], nxt[qb][i >> 3][2 * (i & 7) + 1]));
@@ -814,7 +978,7 @@ __global__ __launch_bounds__(64 * WAVES, 1) void attention_wide_kernel(PvArgs pa
     const float l_tot = l_part[qb] + __shfl_xor(l_part[qb], 32);
     if (qi[qb] >= n_rows) continue;
     const int64_t row = r0 + qi[qb];
-    if (splits > 1) {
+    if (splits > 1 || MASK) {
       const int64_t prow = (int64_t)a.row_start[a.batch];
       float* po = pa.part_o + (((int64_t)split * prow + row) * a.H + h) * kDh;
 #pragma unroll
@@ -963,7 +1127,7 @@ hipError_t launch_attention_bf16(const Ragged& rg, int H, int Hkv, const void* q
       acc += a.row_n[b] / WideQ::kTileQ;
     }
     a.tile_start[rg.batch] = acc;
-    hipLaunchKernelGGL((attention_wide_kernel<kWideQB, kWideWaves>), dim3(acc * H), dim3(WideQ::kThreads), 0, s, pa);
+    hipLaunchKernelGGL((attention_wide_kernel<kWideQB, kWideWaves, false>), dim3(acc * H), dim3(WideQ::kThreads), 0, s, pa);
     acc = 0;
     for (int b = 0; b < rg.batch; ++b) {
       const int nr = a.row_start[b + 1] - a.row_start[b];
@@ -973,7 +1137,7 @@ hipError_t launch_attention_bf16(const Ragged& rg, int H, int Hkv, const void* q
       acc += (a.row_n[b] + kPvTileQ - 1) / kPvTileQ;
     }
     a.tile_start[rg.batch] = acc;
-    hipLaunchKernelGGL(attention_pv_kernel<false>, dim3(acc * H), dim3(kPvThreads), 0, s, pa);
+    hipLaunchKernelGGL(attention_pv_kernel, dim3(acc * H), dim3(kPvThreads), 0, s, pa);
     return hipGetLastError();
   }
   const int tq = wide ? WideQ::kTileQ : kPvTileQ;
@@ -990,10 +1154,10 @@ hipError_t launch_attention_bf16(const Ragged& rg, int H, int Hkv, const void* q
   pa.part_ml = part ? part + (size_t)splits * rows * H * kDh : nullptr;
   if (splits > 1 && a.lse_aff) pa.part_aff = pa.part_ml + (size_t)splits * rows * H * 2;
   if (wide)
-    hipLaunchKernelGGL((attention_wide_kernel<kWideQB, kWideWaves>), dim3(acc_tiles * H * splits),
+    hipLaunchKernelGGL((attention_wide_kernel<kWideQB, kWideWaves, false>), dim3(acc_tiles * H * splits),
                        dim3(WideQ::kThreads), 0, s, pa);
   else
-    hipLaunchKernelGGL(attention_pv_kernel<false>, dim3(acc_tiles * H * splits), dim3(kPvThreads), 0, s, pa);
+    hipLaunchKernelGGL(attention_pv_kernel, dim3(acc_tiles * H * splits), dim3(kPvThreads), 0, s, pa);
   if (splits > 1) {
     const int64_t pairs = rows * H;
     hipLaunchKernelGGL(attention_merge_kernel, dim3((unsigned)((pairs + 7) / 8)), dim3(256), 0, s,
@@ -1021,12 +1185,6 @@ __global__ __launch_bounds__(256) void anchor_mask_kernel(const int32_t* __restr
   for (int i = threadIdx.x; i < n_words; i += 256) mask[(int64_t)b * n_words + i] = words[i];
 }
 
-// Decode-step attention over a view made of the shared affix (minus each
-// request's anchors) and each request's private keys.  Pass 1 takes the
-// queries of all requests together against the shared affix keys, so each
-// K/V tile of the affix is read once per 128 queries instead of once per
-// request; pass 2 takes each request's queries against its private keys.
-// Both write (O, max, sum) partials, which the merge kernel combines.
 hipError_t launch_attention_decode_bf16(int batch, int rows_per_req, int H, int Hkv, const void* q,
                                         const int32_t* affix_slots, int L, const int32_t* anchors, int k,
                                         const int32_t* private_slots, int private_len, const void* k_pool,
@@ -1035,85 +1193,105 @@ hipError_t launch_attention_decode_bf16(int batch, int rows_per_req, int H, int 
   const int64_t rows = (int64_t)batch * rows_per_req;
   if (rows == 0) return hipSuccess;
   const bool shared = L > k;  // some affix position is read from the shared slots
+  const bool priv = private_len > 0;
+  const int rep = H / Hkv;
   const int64_t per_split = rows * H * (kDh * 4 + 8);
-  const int q_tiles_all = (int)((rows + kPvTileQ - 1) / kPvTileQ);
-  const int q_tiles_req = (rows_per_req + kPvTileQ - 1) / kPvTileQ;
-  const int n_kt_shared = (L + kTileK - 1) / kTileK;
-  if ((size_t)per_split * (shared ? 2 : 1) > part_bytes) return hipErrorInvalidValue;
-  const int sp_priv = 1;
-  double cost_unused = 0.0;
-  const int sp_shared = shared ? attention_splits(q_tiles_all * H, 512, 1.0, n_kt_shared, rows, H,
-                                                  part_bytes - (size_t)per_split * sp_priv, 0, &cost_unused)
-                               : 0;
-  const int total = sp_shared + sp_priv;
-
-  auto common = [&](PvArgs& pa) {
-    AttnArgs& a = pa.a;
-    a.q = (const bf16*)q;
-    a.q_ld = (int64_t)H * kDh;
-    a.q_n_rows = rows;
-    a.q_idx = nullptr;
-    a.k_pool = (const bf16*)k_pool;
-    a.v_pool = (const bf16*)v_pool;
-    a.pool_ld = pool_ld;
-    a.n_slots = n_slots;
-    a.out = (bf16*)out;
-    a.lse = nullptr;
-    a.H = H;
-    a.Hkv = Hkv;
-    pa.part_o = part;
-    pa.part_ml = part + (size_t)total * rows * H * kDh;
-    pa.partial = 1;
-    pa.part_rows = rows;
+  const int kt_s = shared ? (L + kTileK - 1) / kTileK : 0, kt_p = (private_len + kTileK - 1) / kTileK;
+  DecArgs a = {};
+  a.tiles_shared = (int)((rows * rep + kPvTileQ - 1) / kPvTileQ);
+  a.tiles_private = (int)(((int64_t)rows_per_req * rep + kPvTileQ - 1) / kPvTileQ);
+  const int64_t wg_s = (int64_t)a.tiles_shared * Hkv, wg_p = (int64_t)batch * a.tiles_private * Hkv;
+  // Estimated time (us): 512 workgroups at a time, 3.2 us a tile (2.4 where a
+  // CU has one workgroup), kinds of unequal length ending on average half a
+  // workgroup apart; the private keys at 5 TB/s at best; each split's
+  // partials written and read at 6 TB/s.
+  const double private_us = (double)batch * private_len * Hkv * kRowB * 2.0 / 5e6;
+  auto narrow_us = [](int64_t n_s, int len_s, int64_t n_p, int len_p) {
+    const int64_t n = n_s + n_p;
+    const double tile = n > 256 ? 3.2 : 2.4;
+    const int len = std::max(len_s, len_p);
+    if (n <= 512) return tile * len;
+    if (n_s == 0 || n_p == 0) return tile * len * (double)((n + 511) / 512);
+    return tile * std::max(((double)n_s * len_s + (double)n_p * len_p) / 512.0 + 0.5 * len, (double)len);
   };
-  if (shared) {
-    hipLaunchKernelGGL(anchor_mask_kernel, dim3(batch), dim3(256), 0, s, anchors, k, L, n_kt_shared, mask);
-    PvArgs pa = {};
-    common(pa);
-    AttnArgs& a = pa.a;
-    a.slots = affix_slots;
-    a.batch = 1;
-    a.row_start[0] = 0;
-    a.row_start[1] = (int)rows;
-    a.row_lo[0] = 0;
-    a.row_n[0] = (int)rows;
-    a.key_start[0] = 0;
-    a.key_start[1] = L;
-    a.key_len[0] = L;
-    a.tile_start[0] = 0;
-    a.tile_start[1] = q_tiles_all;
-    pa.splits = sp_shared;
-    pa.split_base = 0;
-    pa.key_mask = mask;
-    pa.mask_tiles = n_kt_shared;
-    pa.mask_rows = rows_per_req;
-    hipLaunchKernelGGL(attention_pv_kernel<true>, dim3(q_tiles_all * H * sp_shared), dim3(kPvThreads), 0, s, pa);
-  }
-  {
-    PvArgs pa = {};
-    common(pa);
-    AttnArgs& a = pa.a;
-    a.slots = private_slots;
-    a.batch = batch;
-    for (int b = 0; b <= batch; ++b) {
-      a.row_start[b] = b * rows_per_req;
-      if (b < batch) {
-        a.row_lo[b] = 0;
-        a.row_n[b] = rows_per_req;
+  // The shared affix on the 256-query kernel (2.4 us a tile, one workgroup
+  // per CU) in a launch of its own, ahead of the private keys, where that comes
+  // out ahead: 32 x 32 rows, 32 heads, 8192 affix and 2150 private keys 159 +
+  // 222 us, against 208 + 222 with both on 128-query tiles (in one launch or
+  // two: neither kind leaves the other room to run beside it).  A wavefront's
+  // 32 queries have to share a request, and a split's masks to fit in LDS.
+  const bool wide_ok = shared && rows_per_req % 32 == 0 &&
+                       (uint64_t)n_slots * (uint64_t)pool_ld * 2u <= (uint64_t)kWdAbsent;
+  const int64_t tiles_w = (rows + WideQ::kTileQ - 1) / WideQ::kTileQ * H;
+  double best = 1e30;
+  bool wide = false;
+  for (int ss = shared ? 1 : 0; ss <= (shared ? std::min(16, kt_s) : 0); ++ss)
+    for (int sp = priv ? 1 : 0; sp <= (priv ? std::min(16, kt_p) : 0); ++sp) {
+      if ((size_t)(per_split * (ss + sp)) > part_bytes) break;
+      const int len_s = ss ? (kt_s + ss - 1) / ss : 0, len_p = sp ? (kt_p + sp - 1) / sp : 0;
+      const double merge = 2.0 * per_split * (ss + sp) / 6e6;
+      const double one = std::max(private_us, narrow_us(wg_s * ss, len_s, wg_p * sp, len_p));
+      const double two = wide_ok && len_s <= kWdMaskTiles
+                             ? 5.0 + 2.4 * (double)((tiles_w * ss + 255) / 256) * len_s +
+                                   std::max(private_us, narrow_us(0, 0, wg_p * sp, len_p))
+                             : 1e30;
+      if (std::min(one, two) + merge < best) {
+        best = std::min(one, two) + merge;
+        a.sp_shared = ss;
+        a.sp_private = sp;
+        wide = two < one;
       }
-      a.key_start[b] = b * private_len;
-      a.tile_start[b] = b * q_tiles_req;
     }
-    for (int b = 0; b < batch; ++b) a.key_len[b] = private_len;
-    pa.splits = sp_priv;
-    pa.split_base = sp_shared;
-    hipLaunchKernelGGL(attention_pv_kernel<false>, dim3(batch * q_tiles_req * H * sp_priv), dim3(kPvThreads), 0, s,
-                       pa);
+  const int total = a.sp_shared + a.sp_private;
+  if (total == 0) return hipErrorInvalidValue;  // no keys, or no space for the partials
+  a.n_shared = wide ? 0 : (int)(wg_s * a.sp_shared);
+  a.n_private = (int)(wg_p * a.sp_private);
+  a.kv = {(const bf16*)k_pool, (const bf16*)v_pool, pool_ld, n_slots};
+  a.q = (const bf16*)q;
+  a.affix_slots = affix_slots;
+  a.mask = mask;
+  a.private_slots = private_slots;
+  a.part_o = part;
+  a.part_ml = part + (size_t)total * rows * H * kDh;
+  a.L = L;
+  a.private_len = private_len;
+  a.H = H;
+  a.Hkv = Hkv;
+  a.rows = (int)rows;
+  a.rows_per_req = rows_per_req;
+  if (shared)
+    hipLaunchKernelGGL(anchor_mask_kernel, dim3(batch), dim3(256), 0, s, anchors, k, L, kt_s, mask);
+  if (wide) {
+    PvArgs pa = {};
+    AttnArgs& w = pa.a;
+    w.q = a.q;
+    w.q_ld = (int64_t)H * kDh;
+    w.q_n_rows = rows;
+    w.slots = affix_slots;
+    w.k_pool = a.kv.k_pool;
+    w.v_pool = a.kv.v_pool;
+    w.pool_ld = pool_ld;
+    w.n_slots = n_slots;
+    w.H = H;
+    w.Hkv = Hkv;
+    w.batch = 1;
+    w.row_start[1] = w.row_n[0] = (int)rows;
+    w.key_start[1] = w.key_len[0] = L;
+    w.tile_start[1] = (int)((rows + WideQ::kTileQ - 1) / WideQ::kTileQ);
+    pa.splits = a.sp_shared;
+    pa.part_o = a.part_o;
+    pa.part_ml = a.part_ml;
+    pa.key_mask = mask;
+    pa.mask_tiles = kt_s;
+    pa.mask_rows = rows_per_req;
+    hipLaunchKernelGGL((attention_wide_kernel<kWideQB, kWideWaves, true>),
+                       dim3(w.tile_start[1] * H * a.sp_shared), dim3(WideQ::kThreads), 0, s, pa);
   }
+  if (a.n_shared + a.n_private > 0)
+    hipLaunchKernelGGL(attention_decode_kernel, dim3(a.n_shared + a.n_private), dim3(kPvThreads), 0, s, a);
   const int64_t pairs = rows * H;
   hipLaunchKernelGGL(attention_merge_kernel, dim3((unsigned)((pairs + 7) / 8)), dim3(256), 0, s, (const float*)part,
-                     (const float*)(part + (size_t)total * rows * H * kDh), total, rows, H, (bf16*)out, nullptr,
-                     nullptr, nullptr);
+                     (const float*)a.part_ml, total, rows, H, (bf16*)out, nullptr, nullptr, nullptr);
   return hipGetLastError();
 }
 

@@ -206,3 +206,77 @@ def test_layer_few_rows(A, B, blk, H, Hkv, F, d):
     gu = norm(xr, dev["mlp_norm"]) @ D(dev["w_gate_up"]).t()
     xr = xr + (torch.nn.functional.silu(gu[:, :F]) * gu[:, F:]) @ D(dev["w_down"]).t()
     assert_close(down(x), xr.cpu().numpy(), "bf16", "layer rows")
+
+
+# ----------------------------------------------------------------------------- decode-step attention
+
+@pytest.mark.parametrize("H,Hkv,B,blk,L,k,priv", [
+    (4, 4, 1, 32, 1024, 205, 77),     # one request, both kinds split along their keys
+    (4, 4, 3, 20, 200, 40, 30),       # 32 queries of a wavefront across requests: per-lane masks
+    (8, 2, 4, 32, 640, 100, 65),      # grouped heads as further rows of a tile
+    (6, 1, 2, 17, 129, 129, 40),      # every affix key an anchor: private keys alone
+    (4, 2, 2, 32, 130, 0, 32),        # no anchors
+    (32, 32, 8, 32, 2048, 410, 300),  # the 256-query kernel on the shared affix
+    (32, 32, 9, 32, 1031, 700, 33),   # the same, a part-full query tile and key tile, whole tiles masked
+    (32, 8, 16, 64, 4096, 819, 64),   # the same with grouped heads, several requests' rows a tile
+])
+def test_decode_attention(A, H, Hkv, B, blk, L, k, priv):
+    """acache_layer_decode against the block in fp64: the shared affix minus
+    each request's anchors plus its private slots, some of them out of range
+    (zero key, zero value)."""
+    import torch
+    rng = np.random.default_rng(L + H)
+    dh, d, F, M = 128, 256, 256, B * blk
+    shapes = dict(w_qkv=((H + 2 * Hkv) * dh, d), w_o=(d, H * dh), w_gate_up=(2 * F, d), w_down=(d, F))
+    bits = {n: W.draw_tensor(s, "bf16", std=0.08, seed=i) for i, (n, s) in enumerate(shapes.items())}
+    bits["attn_norm"] = bits["mlp_norm"] = W.draw_tensor((d,), "bf16", seed=9)
+    x0 = W.draw_tensor((M, d), "bf16", seed=10)
+    n_slots = L + B * priv + 3
+    kp, vp = (W.draw_tensor((n_slots, Hkv * dh), "bf16", seed=11 + i) for i in range(2))
+    perm = rng.permutation(n_slots)
+    affix, private = perm[:L].copy(), perm[L:L + B * priv].reshape(B, priv).copy()
+    anchors = np.stack([np.sort(rng.permutation(L)[:k]) for _ in range(B)]).astype(np.int32)
+    if k >= 700:  # two whole key tiles of request 0 are anchors
+        rest = rng.permutation(np.concatenate([np.arange(64, 128), np.arange(256, L)]))[:k - 128]
+        anchors[0] = np.sort(np.concatenate([np.arange(0, 64), np.arange(128, 192), rest]))
+    write = private[:, priv - blk:].copy() if priv >= blk else private[:, :0]
+    if priv < blk:
+        write = np.full((B, blk), -1)  # rows whose K/V go nowhere
+    affix[L // 2], private[0, 0] = n_slots + 9, -5
+    pos = rng.integers(0, 9000, size=M)
+    dims = A.make_dims(d, H, Hkv, dh, F, "bf16")
+    dev = {n: up(b, "bf16") for n, b in bits.items()}
+    x, gk, gv = up(x0, "bf16").clone(), up(kp, "bf16").clone(), up(vp, "bf16").clone()
+    ws = A.workspace(dims, M, B, L)
+    run = lambda xx: A.acache_layer_decode(  # noqa: E731
+        dims, dev, B, blk, xx, up_i32(pos), up_i32(write.reshape(-1)), up_i32(affix),
+        up_i32(anchors) if k else None, k, up_i32(private.reshape(-1)), priv, gk, gv, ws)
+    run(x)
+    again = up(x0, "bf16").clone()
+    run(again)
+    assert torch.equal(x, again)  # partials merged in a fixed order
+    D = lambda t: t.double()  # noqa: E731
+    norm = lambda t, g: t / torch.sqrt((t * t).mean(1, keepdim=True) + 1e-5) * D(g)  # noqa: E731
+    xr = D(up(x0, "bf16"))
+    q = (norm(xr, dev["attn_norm"]) @ D(dev["w_qkv"]).t()[:, :H * dh]).view(M, H, dh)
+    th = 10000.0 ** (-2.0 * torch.arange(64, device="cuda", dtype=torch.float64) / dh)
+    an = torch.from_numpy(pos).cuda().double()[:, None, None] * th
+    q = torch.cat([q[..., :64] * an.cos() - q[..., 64:] * an.sin(), q[..., 64:] * an.cos() + q[..., :64] * an.sin()], 2)
+    # the keys as stored (the rows' own K/V, checked by the projection's tests)
+    zero = torch.zeros(1, Hkv * dh, dtype=torch.float64, device="cuda")
+    K, V = torch.cat([D(gk), zero]), torch.cat([D(gv), zero])
+    o = torch.zeros(M, H * dh, dtype=torch.float64, device="cuda")
+    for b in range(B):
+        keep = np.ones(L, bool)
+        keep[anchors[b]] = False
+        view = np.concatenate([affix[keep], private[b]])
+        sl = torch.from_numpy(np.where((view < 0) | (view >= n_slots), n_slots, view)).cuda().long()
+        kb, vb = K[sl], V[sl]
+        for h in range(H):
+            g = slice(h // (H // Hkv) * dh, (h // (H // Hkv) + 1) * dh)
+            lg = q[b * blk:(b + 1) * blk, h] @ kb[:, g].t() / np.sqrt(dh)
+            o[b * blk:(b + 1) * blk, h * dh:(h + 1) * dh] = torch.softmax(lg, 1) @ vb[:, g]
+    xr = xr + o @ D(dev["w_o"]).t()
+    gu = norm(xr, dev["mlp_norm"]) @ D(dev["w_gate_up"]).t()
+    xr = xr + (torch.nn.functional.silu(gu[:, :F]) * gu[:, F:]) @ D(dev["w_down"]).t()
+    assert_close(down(x), xr.cpu().numpy(), "bf16", "decode rows")
