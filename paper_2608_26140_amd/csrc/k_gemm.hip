@@ -67,6 +67,12 @@ struct Cfg {
   static_assert(BN * CPR % THREADS == 0 && BM * CPR % THREADS == 0, "load split");
 };
 
+// The 4-wave kernel's other tiles (2 x 2 waves of BN / 2 x BM / 2).
+template <int BN_, int BM_>
+struct Tile4 {
+  static constexpr int BN = BN_, BM = BM_, WN = 2, WM = 2, BK = 64, WAVES = 4, THREADS = 256;
+};
+
 typedef __attribute__((__vector_size__(4 * sizeof(uint32_t)))) uint32_t u32x4;
 
 struct TileMap {
@@ -486,38 +492,55 @@ __device__ __forceinline__ void mfma16x16x32_agpr(f32x4& c, bf16x8 a, bf16x8 b) 
 // VALU-written AGPRs and a following MFMA), more than any gfx950 MFMA needs.
 __device__ __forceinline__ void mfma_agpr_fence() { asm volatile("s_nop 7\n s_nop 7\n s_nop 7" ::: "memory"); }
 
-// One wave's 128 x 128 accumulators: acc[a][b][r] = C[m = mbase + 16 b + lane % 16]
-// [n = nbase + 16 a + 4 (lane / 16) + r].
-typedef f32x4 Acc16[8][8];
-
-// Partial accumulators: float4 chunk i = a * 8 + b of lane l at (i * 64 + l) * 4.
-__device__ __forceinline__ void store_partial16(float* base, const Acc16& acc, int lane) {
+// One wave's accumulators: acc[a][b][r] = C[m = mbase + 16 b + lane % 16]
+// [column 4 (lane / 16) + r of weight fragment a].
+// Partial accumulators of a 128 x 128 wave tile: float4 chunk i = a * 8 + b of
+// lane l at (i * 64 + l) * 4.
+__device__ __forceinline__ void store_partial16(float* base, const f32x4 (&acc)[8][8], int lane) {
 #pragma unroll
   for (int a = 0; a < 8; ++a)
 #pragma unroll
     for (int b = 0; b < 8; ++b) *reinterpret_cast<f32x4*>(base + ((a * 8 + b) * 64 + lane) * 4) = acc[a][b];
 }
 
-// Writes one wave's accumulators (wave (wn, wm) of 256 x 256 tile (nt, mt),
-// split sp): the same epilogues as the 32x32 layout.  acc[a][bb] holds the
-// 16-row block b = B0 + bb (NB of the wave's 8).
-template <int EPI, int B0 = 0, int NB = 8>
-__device__ __forceinline__ void epilogue16(const GemmParams& p, const f32x4 (&acc)[8][NB], int nt, int mt, int sp,
+// First weight row of fragment a of wave column wn in N tile nt, NA fragments
+// of 16 rows a wave.  The pair epilogues hold the first members of 16 pairs in
+// fragments 0 .. NA / 2 - 1 and their partners (rotary: + 64 rows of the head,
+// SwiGLU: the up projection) in the rest.  Fragments past the last row repeat
+// the last one; the epilogue skips them.
+template <int EPI, int NA>
+__device__ __forceinline__ int frag_row16(int nt, int wn, int a, int N) {
+  if constexpr (EPI == EPI_SWIGLU || EPI == EPI_QKV) {
+    const int g = min((nt * 2 + wn) * (NA / 2) + a % (NA / 2), N / 32 - 1);
+    const bool second = a >= NA / 2;
+    if constexpr (EPI == EPI_SWIGLU) return g * 16 + (second ? N >> 1 : 0);
+    return (g >> 2) * 128 + (g & 3) * 16 + (second ? 64 : 0);
+  } else {
+    return min((nt * 2 + wn) * NA + a, N / 16 - 1) * 16;
+  }
+}
+
+// Writes one wave's accumulators (wave (wn, wm) of tile (nt, mt), split sp; NA
+// x NBW fragments a wave): the same epilogues as the 32x32 layout.
+// acc[a][bb] holds the 16-row block b = B0 + bb (NB of the wave's NBW).
+template <int EPI, int NA = 8, int NBW = 8, int B0 = 0, int NB = 8>
+__device__ __forceinline__ void epilogue16(const GemmParams& p, const f32x4 (&acc)[NA][NB], int nt, int mt, int sp,
                                            int wn, int wm, int lane) {
   // lane-dependent addresses are computed here, per item: hoisted out of the
   // item loop they would be held through the K loop and spilled
   lane = lane_id_here();
   const int q4 = 4 * (lane >> 4);
-  const int mbase = mt * 256 + wm * 128 + (lane & 15);
+  const int mbase = mt * (32 * NBW) + wm * (16 * NBW) + (lane & 15);
 #pragma unroll
   for (int b = 0; b < NB; ++b) {
     const int m = mbase + (B0 + b) * 16;
     if (m >= p.M) continue;
     if constexpr (EPI == EPI_STORE || EPI == EPI_ACCUM || EPI == EPI_PARTIAL) {
-      const int nbase = nt * 256 + wn * 128 + q4;
+      const int f0 = (nt * 2 + wn) * NA;
 #pragma unroll
-      for (int a = 0; a < 8; ++a) {
-        const int n = nbase + a * 16;
+      for (int a = 0; a < NA; ++a) {
+        if (NA != 8 && (f0 + a) * 16 >= p.N) continue;
+        const int n = (f0 + a) * 16 + q4;
         float v[4] = {acc[a][b][0], acc[a][b][1], acc[a][b][2], acc[a][b][3]};
         if constexpr (EPI == EPI_PARTIAL) {
           *reinterpret_cast<f32x4*>(p.P + ((int64_t)sp * p.M + m) * p.N + n) = acc[a][b];
@@ -532,56 +555,83 @@ __device__ __forceinline__ void epilogue16(const GemmParams& p, const f32x4 (&ac
         }
       }
     } else if constexpr (EPI == EPI_SWIGLU) {
-      // tiles 0..3 of the wave are gate rows, 4..7 the matching up rows
-      const int cbase = nt * 128 + wn * 64 + q4;
+      // fragments 0 .. NA / 2 - 1 of the wave are gate rows, the rest the matching up rows
+      const int g0 = (nt * 2 + wn) * (NA / 2);
 #pragma unroll
-      for (int a = 0; a < 4; ++a) {
+      for (int a = 0; a < NA / 2; ++a) {
+        if (NA != 8 && (g0 + a) * 32 >= p.N) continue;
         float v[4];
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
-          const float gt = acc[a][b][j], up = acc[a + 4][b][j];
+          const float gt = acc[a][b][j], up = acc[a + NA / 2][b][j];
           v[j] = silu_mul(gt, up);
         }
-        store4((bf16*)p.C + (int64_t)m * p.ldc + cbase + a * 16, v);
+        store4((bf16*)p.C + (int64_t)m * p.ldc + (g0 + a) * 16 + q4, v);
       }
     } else if constexpr (EPI == EPI_QKV) {
-      const int col0 = nt * 256 + wn * 128;  // first weight row of this wave = one head
-      const bool is_v = col0 >= p.hq_cols + p.hkv_cols;
-      bf16* dst;
-      if (col0 < p.hq_cols) {
-        dst = (bf16*)p.q_out + (int64_t)m * p.hq_cols + col0;
-      } else {
-        const int64_t slot = p.write_slots[m];
-        if (slot < 0 || slot >= p.n_slots) continue;
-        const int c = is_v ? col0 - p.hq_cols - p.hkv_cols : col0 - p.hq_cols;
-        dst = (bf16*)(is_v ? p.v_pool : p.k_pool) + slot * p.pool_ld + c;
-      }
-      if (!is_v) {
-        // rotate the pairs (d, d + 64): both halves sit in this lane, in
-        // tiles a and a + 4
-        const float* rt = p.rope_cs + (int64_t)m * 128;
+      // The rotary pairs (d, d + 64) sit in this lane, in fragments a and
+      // a + NA / 2.
+      const float* rt = p.rope_cs + (int64_t)m * 128;
+      auto rotate = [&](bf16* dst, int a, int d0) {
+        float lo[4], hi[4];
+        const f32x4 t0 = *reinterpret_cast<const f32x4*>(rt + 2 * d0);
+        const f32x4 t1 = *reinterpret_cast<const f32x4*>(rt + 2 * d0 + 4);
+        const float cs4[4] = {t0[0], t0[2], t1[0], t1[2]}, sn4[4] = {t0[1], t0[3], t1[1], t1[3]};
 #pragma unroll
-        for (int a = 0; a < 4; ++a) {
-          float lo[4], hi[4];
-          const int d0 = a * 16 + q4;
-          const f32x4 t0 = *reinterpret_cast<const f32x4*>(rt + 2 * d0);
-          const f32x4 t1 = *reinterpret_cast<const f32x4*>(rt + 2 * d0 + 4);
-          const float cs4[4] = {t0[0], t0[2], t1[0], t1[2]}, sn4[4] = {t0[1], t0[3], t1[1], t1[3]};
+        for (int j = 0; j < 4; ++j) {
+          const float cs = cs4[j], sn = sn4[j];
+          const float x1 = acc[a][b][j], x2 = acc[a + NA / 2][b][j];
+          lo[j] = x1 * cs - x2 * sn;
+          hi[j] = x2 * cs + x1 * sn;
+        }
+        store4(dst + d0, lo);
+        store4(dst + d0 + 64, hi);
+      };
+      auto plain = [&](bf16* dst, int a) {
+        const float v[4] = {acc[a][b][0], acc[a][b][1], acc[a][b][2], acc[a][b][3]};
+        store4(dst, v);
+      };
+      if constexpr (NA == 8) {  // the wave's 128 weight rows are one head's
+        const int col0 = nt * 256 + wn * 128;
+        const bool is_v = col0 >= p.hq_cols + p.hkv_cols;
+        bf16* dst;
+        if (col0 < p.hq_cols) {
+          dst = (bf16*)p.q_out + (int64_t)m * p.hq_cols + col0;
+        } else {
+          const int64_t slot = p.write_slots[m];
+          if (slot < 0 || slot >= p.n_slots) continue;
+          const int c = is_v ? col0 - p.hq_cols - p.hkv_cols : col0 - p.hq_cols;
+          dst = (bf16*)(is_v ? p.v_pool : p.k_pool) + slot * p.pool_ld + c;
+        }
+        if (!is_v) {
 #pragma unroll
-          for (int j = 0; j < 4; ++j) {
-            const float cs = cs4[j], sn = sn4[j];
-            const float x1 = acc[a][b][j], x2 = acc[a + 4][b][j];
-            lo[j] = x1 * cs - x2 * sn;
-            hi[j] = x2 * cs + x1 * sn;
-          }
-          store4(dst + a * 16 + q4, lo);
-          store4(dst + (a + 4) * 16 + q4, hi);
+          for (int a = 0; a < 4; ++a) rotate(dst, a, a * 16 + q4);
+        } else {
+#pragma unroll
+          for (int a = 0; a < 8; ++a) plain(dst + a * 16 + q4, a);
         }
       } else {
 #pragma unroll
-        for (int a = 0; a < 8; ++a) {
-          const float v[4] = {acc[a][b][0], acc[a][b][1], acc[a][b][2], acc[a][b][3]};
-          store4(dst + a * 16 + q4, v);
+        for (int a = 0; a < NA / 2; ++a) {  // groups of 16 pairs, of up to two heads
+          const int g = (nt * 2 + wn) * (NA / 2) + a;
+          if (g * 32 >= p.N) continue;
+          const int col0 = (g >> 2) * 128, d0 = (g & 3) * 16 + q4;
+          const bool is_v = col0 >= p.hq_cols + p.hkv_cols;
+          bf16* dst;
+          if (col0 < p.hq_cols) {
+            dst = (bf16*)p.q_out + (int64_t)m * p.hq_cols + col0;
+          } else {
+            const int64_t slot = p.write_slots[m];
+            if (slot < 0 || slot >= p.n_slots) continue;
+            const int c = is_v ? col0 - p.hq_cols - p.hkv_cols : col0 - p.hq_cols;
+            dst = (bf16*)(is_v ? p.v_pool : p.k_pool) + slot * p.pool_ld + c;
+          }
+          if (!is_v) {
+            rotate(dst, a, d0);
+          } else {
+            plain(dst + d0, a);
+            plain(dst + d0 + 64, a + NA / 2);
+          }
         }
       }
     }
@@ -589,8 +639,10 @@ __device__ __forceinline__ void epilogue16(const GemmParams& p, const f32x4 (&ac
 }
 
 // Main loop with one wave per SIMD: 4 waves (2 along N x 2 along M), each a
-// 128 x 128 wave tile = 8 x 8 MFMA 16x16x32 tiles, 256 fp32 accumulators
-// per lane (0.5 KB of LDS fragment reads per 32 x 32 x 16 of work).
+// wave tile of NA x NB MFMA 16x16x32 tiles; 8 x 8 (a 256 x 256 workgroup
+// tile), 256 fp32 accumulators per lane and 0.5 KB of LDS fragment reads per
+// 32 x 32 x 16 of work, or with NA or NB or both 6 (192) where those tiles
+// fill the rounds of CUs better.  Figures below are for 8 x 8.
 //
 // LDS holds the 256 weight rows of three 64-wide K steps and the 256
 // activation rows of two, rows of 128 bytes (160 KB in all).  Each copy
@@ -609,37 +661,39 @@ __device__ __forceinline__ void epilogue16(const GemmParams& p, const f32x4 (&ac
 // LDS path carries the same load in both units, and step j + 1 is complete
 // once no more than step j + 2's weight copies are in flight.
 constexpr int kW4RowB = 128;
-constexpr int kW4StageB = 256 * kW4RowB;  // one operand's rows of one K step
 
 template <int EPI, class C>
 __global__ __launch_bounds__(C::THREADS, 1) void gemm_bf16_w4_kernel(GemmParams p, TileMap tm) {
-  static_assert(C::BN == 256 && C::BM == 256 && C::WN == 2 && C::WM == 2 && C::BK == 64, "4-wave tile");
+  static_assert(C::WN == 2 && C::WM == 2 && C::BK == 64, "4-wave tile");
+  constexpr int NA = C::BN / 32, NB = C::BM / 32;   // fragments of a wave
+  constexpr int kWB = C::BN * kW4RowB, kXB = C::BM * kW4RowB;  // one K step's rows of each operand
+  constexpr int CW = NA, CX = NB;                    // copies of a wave and step (even: whole fragments)
+  constexpr bool kFull = NA == 8 && NB == 8;         // the tile of the stream-K schedule
   // weight stages 0..2, then activation stages 0..1
-  __shared__ __attribute__((aligned(1024))) char ring[5 * kW4StageB];
-  char* const xring = ring + 3 * kW4StageB;
+  __shared__ __attribute__((aligned(1024))) char ring[3 * kWB + 2 * kXB];
+  char* const xring = ring + 3 * kWB;
 
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wn = wave & 1, wm = wave >> 1;
-  const int F = p.N >> 1;
   const int K = p.K;
   const int nk_tile = tm.nk;
   const int w = logical_block();
 
-  // copies: instruction i of a wave covers rows 64 wave + 8 i + lane / 8;
+  // copies: instruction i of a wave covers rows 8 CW wave + 8 i + lane / 8 (CX for activations);
   // the lane fills physical chunk lane % 8 with logical chunk
   // (lane % 8) ^ ((row >> 1) & 7)
   const int crow = lane >> 3;
   // fragment reads: row lane % 16 of each 16-row fragment, chunk 4 h + lane / 16
   const int fsw = ((lane & 15) >> 1) & 7;
-  const int arow = wn * 128 + (lane & 15);
-  const int brow = wm * 128 + (lane & 15);
+  const int arow = wn * 16 * NA + (lane & 15);
+  const int brow = wm * 16 * NB + (lane & 15);
   const int cofs0 = ((0 + (lane >> 4)) ^ fsw) * 16;
   const int cofs1 = ((4 + (lane >> 4)) ^ fsw) * 16;
   const __amdgpu_buffer_rsrc_t wres = buffer_rsrc(p.W, (uint32_t)p.N * (uint32_t)K * 2u);
   const __amdgpu_buffer_rsrc_t xres = buffer_rsrc(p.X, (uint32_t)p.M * (uint32_t)K * 2u);
 
-  Acc16 acc;
+  f32x4 acc[NA][NB];
   int item = 0;
   int u = 0, u_end = 0;
   if (tm.sk_groups > 0 && w < tm.sk_groups) {
@@ -678,40 +732,52 @@ __global__ __launch_bounds__(C::THREADS, 1) void gemm_bf16_w4_kernel(GemmParams 
     // compiler cannot hoist: hoisted out of the item loop they are held
     // through the K loop, spilled, and reloaded one wait at a time
     const int ln = lane_id_here();
-    uint32_t wsrc[8], xsrc[8];
+    uint32_t wsrc[CW], xsrc[CX];
 #pragma unroll
-    for (int i = 0; i < 8; ++i) {
-      const int r = wave * 64 + i * 8 + (ln >> 3);
+    for (int i = 0; i < CW; ++i) {
+      const int r = wave * 8 * CW + i * 8 + (ln >> 3);
       const int c = (ln & 7) ^ ((4 * i + (ln >> 4)) & 7);
-      wsrc[i] = (uint32_t)(weight_row<EPI, 256>(nt, r, F) * K + k0 + c * 8) * 2u;
+      int row;
+      if constexpr (NA == 8) {
+        row = weight_row<EPI, 256>(nt, r, p.N >> 1);
+      } else {
+        const int f = (wave * 8 * CW + i * 8) >> 4;  // uniform: an instruction's rows lie in one fragment
+        row = frag_row16<EPI, NA>(nt, f / NA, f % NA, p.N) + (r & 15);
+      }
+      wsrc[i] = (uint32_t)(row * K + k0 + c * 8) * 2u;
+    }
+#pragma unroll
+    for (int i = 0; i < CX; ++i) {
+      const int r = wave * 8 * CX + i * 8 + (ln >> 3);
+      const int c = (ln & 7) ^ ((4 * i + (ln >> 4)) & 7);
       xsrc[i] = (uint32_t)(min(mt * C::BM + r, p.M - 1) * K + k0 + c * 8) * 2u;
     }
-    // copy i (0..7) of K step j: 8 weight rows into weight stage j % 3, or
-    // 8 activation rows into activation stage j % 2
+    // copy i of K step j: 8 weight rows into weight stage j % 3, or 8
+    // activation rows into activation stage j % 2
     auto copy_w = [&](int j, int i) {
-      dma16_buf(wres, wsrc[i], (uint32_t)j * 128u, ring + (j % 3) * kW4StageB + (wave * 64 + i * 8) * kW4RowB);
+      dma16_buf(wres, wsrc[i], (uint32_t)j * 128u, ring + (j % 3) * kWB + (wave * CW + i) * 8 * kW4RowB);
     };
     auto copy_x = [&](int j, int i) {
-      dma16_buf(xres, xsrc[i], (uint32_t)j * 128u, xring + (j & 1) * kW4StageB + (wave * 64 + i * 8) * kW4RowB);
+      dma16_buf(xres, xsrc[i], (uint32_t)j * 128u, xring + (j & 1) * kXB + (wave * CX + i) * 8 * kW4RowB);
     };
     auto issue = [&](int j) {
 #pragma unroll
-      for (int i = 0; i < 8; ++i) copy_w(j, i);
+      for (int i = 0; i < CW; ++i) copy_w(j, i);
 #pragma unroll
-      for (int i = 0; i < 8; ++i) copy_x(j, i);
+      for (int i = 0; i < CX; ++i) copy_x(j, i);
     };
-    // fragment f of unit h (0 / 1) of step j: f < 8 weight tile f, else
-    // activation tile f - 8
+    // fragment f of unit h (0 / 1) of step j: f < NA weight fragment f, else
+    // activation fragment f - NA
     auto frag = [&](int j, int h, int f) {
-      const char* st = f < 8 ? ring + (j % 3) * kW4StageB : xring + (j & 1) * kW4StageB;
-      const int row = f < 8 ? arow + f * 16 : brow + (f - 8) * 16;
+      const char* st = f < NA ? ring + (j % 3) * kWB : xring + (j & 1) * kXB;
+      const int row = f < NA ? arow + f * 16 : brow + (f - NA) * 16;
       return *reinterpret_cast<const bf16x8*>(st + row * kW4RowB + (h ? cofs1 : cofs0));
     };
 
 #pragma unroll
-    for (int a = 0; a < 8; ++a)
+    for (int a = 0; a < NA; ++a)
 #pragma unroll
-      for (int b = 0; b < 8; ++b)
+      for (int b = 0; b < NB; ++b)
 #pragma unroll
         for (int r = 0; r < 4; ++r) acc[a][b][r] = 0.f;
 
@@ -724,35 +790,40 @@ __global__ __launch_bounds__(C::THREADS, 1) void gemm_bf16_w4_kernel(GemmParams 
     issue(0);
     if (kn > 1) {
       issue(1);
-      wait_vmcnt<16>();  // step 0 (this wave's part)
+      wait_vmcnt<CW + CX>();  // step 0 (this wave's part)
     } else {
       wait_vmcnt<0>();
     }
     __builtin_amdgcn_sched_barrier(0);
     bare_barrier();
     __builtin_amdgcn_sched_barrier(0);
-    bf16x8 fx[16], fy[16];
+    constexpr int NF = NA + NB, T = NA * NB;  // fragments, MFMAs of a unit
+    bf16x8 fx[NF], fy[NF];
 #pragma unroll
-    for (int f = 0; f < 16; ++f) fx[f] = frag(0, 0, f);
+    for (int f = 0; f < NF; ++f) fx[f] = frag(0, 0, f);
     mfma_agpr_fence();  // the zeroed accumulators before the first MFMA
 
-    // 64 MFMAs from cur, the 16 reads of the next unit into nxt among the
-    // first 46,
-    // and (copies) the 8 weight (CX false) or activation (CX true) copies of
-    // K step cj, one after every eighth MFMA (a burst of copies stalls the
-    // wave's MFMA issue while the memory pipeline takes them)
-    auto unit = [&](bf16x8 (&cur)[16], bf16x8 (&nxt)[16], int nj, int nh, int cj, auto cx, auto copies) {
+    // T MFMAs from cur, the reads of the next unit into nxt among the first T -
+    // 16 (64 MFMAs: one every third), and (copies) the weight (CX false) or
+    // activation (CX true) copies of K step cj spread evenly among them (64
+    // MFMAs: one after every eighth; a burst of copies stalls the wave's MFMA
+    // issue while the memory pipeline takes them)
+    auto unit = [&](bf16x8 (&cur)[NF], bf16x8 (&nxt)[NF], int nj, int nh, int cj, auto cx, auto copies) {
+      constexpr bool X = decltype(cx)::value;
+      constexpr int every = T / (X ? CX : CW);
 #pragma unroll
-      for (int i = 0; i < 64; ++i) {
-        const int a = i >> 3, b = i & 7;
+      for (int i = 0; i < T; ++i) {
+        const int a = i / NB, b = i % NB;
         if constexpr (decltype(copies)::value) {
-          if ((i & 7) == 3) {
-            if constexpr (decltype(cx)::value) copy_x(cj, i >> 3);
-            else copy_w(cj, i >> 3);
+          if (i % every == 3 && i / every < (X ? CX : CW)) {
+            if constexpr (X) copy_x(cj, i / every);
+            else copy_w(cj, i / every);
           }
         }
-        if (i % 3 == 0 && i / 3 < 16) nxt[i / 3] = frag(nj, nh, i / 3);
-        mfma16x16x32_agpr(acc[a][b], cur[a], cur[8 + b]);
+#pragma unroll
+        for (int f = 0; f < NF; ++f)
+          if (i == f * (T - 16) / NF) nxt[f] = frag(nj, nh, f);
+        mfma16x16x32_agpr(acc[a][b], cur[a], cur[NA + b]);
         __builtin_amdgcn_sched_barrier(0);
       }
     };
@@ -769,7 +840,7 @@ __global__ __launch_bounds__(C::THREADS, 1) void gemm_bf16_w4_kernel(GemmParams 
       // unit 1 of step j: step j + 1 complete in every wave (copies complete
       // in issue order: in flight after it only step j + 2's weight rows),
       // step j's activation stage free for step j + 2's
-      wait_vmcnt<CP ? 8 : 0>();
+      wait_vmcnt<CP ? CW : 0>();
       wait_lgkmcnt<0>();
       __builtin_amdgcn_sched_barrier(0);
       bare_barrier();
@@ -791,13 +862,17 @@ __global__ __launch_bounds__(C::THREADS, 1) void gemm_bf16_w4_kernel(GemmParams 
     wait_vmcnt<0>();
     lds_barrier();
 
-    if (sk && kn < nk_tile) {
-      float* slot = tm.sk_part + ((size_t)(w * 2 + piece) * C::WAVES + wave) * (64 * 256);
-      store_partial16(slot, acc, lane);
-      ++piece;
+    if constexpr (kFull) {
+      if (sk && kn < nk_tile) {
+        float* slot = tm.sk_part + ((size_t)(w * 2 + piece) * C::WAVES + wave) * (64 * 256);
+        store_partial16(slot, acc, lane);
+        ++piece;
+      } else {
+        if (sk) ++piece;
+        epilogue16<EPI>(p, acc, nt, mt, sp, wn, wm, lane);
+      }
     } else {
-      if (sk) ++piece;
-      epilogue16<EPI>(p, acc, nt, mt, sp, wn, wm, lane);
+      epilogue16<EPI, NA, NB, 0, NB>(p, acc, nt, mt, sp, wn, wm, lane);
     }
   }
 }
@@ -844,7 +919,7 @@ __global__ __launch_bounds__(256) void gemm_bf16_fixup16(GemmParams p, TileMap t
 #pragma unroll
           for (int r = 0; r < 4; ++r) acc[a][bb][r] += v[a][bb][r];
     }
-    epilogue16<EPI, 2 * Q, 2>(p, acc, nt, mt, sp, wn, wm, lane);
+    epilogue16<EPI, 8, 8, 2 * Q, 2>(p, acc, nt, mt, sp, wn, wm, lane);
   };
   switch (q) {
     case 0: run(std::integral_constant<int, 0>()); break;
@@ -910,9 +985,12 @@ __global__ __launch_bounds__(256) void gemm_bf16_fixup(GemmParams p, TileMap tm)
 
 // The 256 x 128 tile (8 waves, 1.25 KB of LDS reads per 32x32x16 MFMA)
 // doubles the tile count for row counts that would leave CUs idle.
-// 256 x 256 tiles: 4 waves of 128 x 128 on 16x16x32 MFMAs (gemm_bf16_w4_kernel);
+// 256 or 192 squared tiles: 4 waves on 16x16x32 MFMAs (gemm_bf16_w4_kernel);
 // 256 x 128 tiles: the 8-wave ping-pong kernel on 32x32x16 MFMAs
 using GemmCfg = Cfg<256, 256, 2, 2, 64>;
+using GemmCfgN = Tile4<192, 256>;   // 192 weight rows x 256 activation rows
+using GemmCfgM = Tile4<256, 192>;
+using GemmCfgS = Tile4<192, 192>;
 using GemmCfgH = Cfg<256, 128, 2, 4, 64>;
 
 namespace {
@@ -921,6 +999,8 @@ namespace {
 // at the same number of busy CUs (measured 0.65 - 0.71: the half tile reads
 // more LDS bytes per MFMA).
 constexpr double kHalfStep = 0.7;
+// ... of a 192 x 256 or 256 x 192, and of a 192 x 192 tile.
+constexpr double kNarrowStep = 0.84, kSquareStep = 0.68;
 
 int cu_count() {
   static std::atomic<int> cached[64];
@@ -935,9 +1015,16 @@ int cu_count() {
   return n;
 }
 
+// Time of one K step relative to one of a 256 x 256 tile.
 template <class C>
 constexpr double step_cost() {
-  return C::BM == 256 ? 1.0 : kHalfStep;
+  if (C::WAVES == 8) return kHalfStep;
+  return C::BN == 256 && C::BM == 256 ? 1.0 : C::BN == 192 && C::BM == 192 ? kSquareStep : kNarrowStep;
+}
+// The stream-K schedule's pieces and fixup kernels are built for these tiles.
+template <class C>
+constexpr bool has_stream_k() {
+  return C::WAVES == 8 || (C::BN == 256 && C::BM == 256);
 }
 
 // K splits for the split-K partial epilogue, and their cost in 256 x 256 K
@@ -948,7 +1035,7 @@ constexpr double step_cost() {
 // divide nk; each keeps at least kMinSkSteps steps.
 template <class C>
 int splits_for(int M, int N, int K, double* cost_out) {
-  const int tiles = ((M + C::BM - 1) / C::BM) * (N / C::BN);
+  const int tiles = ((M + C::BM - 1) / C::BM) * ((N + C::BN - 1) / C::BN);
   const int nk = K / C::BK;
   const int G = kMaxSkGroups;
   const double slice = (double)M * N * 8.0 / 9.5e6;
@@ -966,13 +1053,35 @@ int splits_for(int M, int N, int K, double* cost_out) {
   return best;
 }
 
-// The split-K epilogue's tile: a function of the shape only, so that the
-// caller's split count (which sizes its partial buffer) and the launch agree.
-bool partial_half(int M, int N, int K) {
-  double c256 = 0, c128 = 0;
-  splits_for<GemmCfg>(M, N, K, &c256);
-  splits_for<GemmCfgH>(M, N, K, &c128);
-  return c128 < c256;
+// The split-K epilogue's tile and splits: a function of the shape only, so that
+// the caller's split count (which sizes its partial buffer) and the launch
+// agree.
+enum TileId { TILE_256, TILE_HALF, TILE_N, TILE_M, TILE_S };
+struct PartialPlan {
+  TileId tile;
+  int splits;
+};
+PartialPlan partial_plan(int M, int N, int K) {
+  PartialPlan best = {TILE_256, 1};
+  double best_cost = 1e30;
+  auto consider = [&](TileId id, int splits, double cost) {
+    if (cost < best_cost) {
+      best_cost = cost;
+      best = {id, splits};
+    }
+  };
+  double c = 0;
+  int s = splits_for<GemmCfg>(M, N, K, &c);
+  consider(TILE_256, s, c);
+  s = splits_for<GemmCfgH>(M, N, K, &c);
+  consider(TILE_HALF, s, c);
+  s = splits_for<GemmCfgN>(M, N, K, &c);
+  consider(TILE_N, s, c);
+  s = splits_for<GemmCfgM>(M, N, K, &c);
+  consider(TILE_M, s, c);
+  s = splits_for<GemmCfgS>(M, N, K, &c);
+  consider(TILE_S, s, c);
+  return best;
 }
 
 struct Plan {
@@ -987,7 +1096,7 @@ Plan plan_cfg(GemmEpi epi, const GemmParams& p) {
   Plan pl = {};
   TileMap& tm = pl.tm;
   tm.m_tiles = (p.M + C::BM - 1) / C::BM;
-  tm.n_tiles = epi == EPI_SWIGLU ? (p.N / 2) / (C::BN / 2) : p.N / C::BN;
+  tm.n_tiles = (p.N + C::BN - 1) / C::BN;
   tm.splits = epi == EPI_PARTIAL ? p.splits : 1;
   tm.nk = p.K / C::BK;
   const int tiles = tm.m_tiles * tm.n_tiles * tm.splits;
@@ -999,7 +1108,7 @@ Plan plan_cfg(GemmEpi epi, const GemmParams& p) {
   tm.dp_tiles = tiles;
   const double dp_cost = (double)((tiles + G - 1) / G) * ((nk + tm.splits - 1) / tm.splits);
   double best = dp_cost;
-  if (epi != EPI_PARTIAL && p.sk_ws && nk >= kMinSkSteps) {
+  if (has_stream_k<C>() && epi != EPI_PARTIAL && p.sk_ws && nk >= kMinSkSteps) {
     // Stream-K with g workgroups on the e tiles left after r full rounds:
     // r whole tiles, ceil(e nk / g) steps, and the partial pieces (at most
     // e + g, each written and read back once), which cost about 1/8 of a K
@@ -1064,7 +1173,9 @@ hipError_t launch_plan(GemmEpi epi, const GemmParams& p, const Plan& pl, hipStre
   }
   if (pl.sk_tiles > 0) {
     const dim3 fgrid(pl.sk_tiles * C::WAVES), fblock(256);
-    if constexpr (C::WAVES == 4) {
+    if constexpr (!has_stream_k<C>()) {
+      return hipErrorInvalidValue;  // never planned
+    } else if constexpr (C::WAVES == 4) {
       switch (epi) {
         case EPI_STORE: hipLaunchKernelGGL((gemm_bf16_fixup16<EPI_STORE, C>), fgrid, fblock, 0, s, p, tm); break;
         case EPI_ACCUM: hipLaunchKernelGGL((gemm_bf16_fixup16<EPI_ACCUM, C>), fgrid, fblock, 0, s, p, tm); break;
@@ -1089,7 +1200,7 @@ hipError_t launch_plan(GemmEpi epi, const GemmParams& p, const Plan& pl, hipStre
 
 int gemm_bf16_splits(int M, int N, int K) {
   if (M <= kRowsMax) return gemm_rows_splits(M, N, K);
-  return partial_half(M, N, K) ? splits_for<GemmCfgH>(M, N, K, nullptr) : splits_for<GemmCfg>(M, N, K, nullptr);
+  return partial_plan(M, N, K).splits;
 }
 
 size_t gemm_bf16_sk_ws_bytes() {
@@ -1098,24 +1209,41 @@ size_t gemm_bf16_sk_ws_bytes() {
 }
 
 hipError_t launch_gemm_bf16(GemmEpi epi, const GemmParams& p, hipStream_t s) {
-  bool half;
+  if (epi == EPI_PARTIAL && p.M <= kRowsMax) return launch_gemm_rows(epi, p, s);
+  TileId tile = TILE_256;
+  const Plan p256 = plan_cfg<GemmCfg>(epi, p), p128 = plan_cfg<GemmCfgH>(epi, p);
+  const Plan pn = plan_cfg<GemmCfgN>(epi, p), pm = plan_cfg<GemmCfgM>(epi, p), ps = plan_cfg<GemmCfgS>(epi, p);
   if (epi == EPI_PARTIAL) {
-    if (p.M <= kRowsMax) return launch_gemm_rows(epi, p, s);
-    half = partial_half(p.M, p.N, p.K);
+    tile = partial_plan(p.M, p.N, p.K).tile;
   } else {
-    const double c256 = plan_cfg<GemmCfg>(epi, p).cost, c128 = plan_cfg<GemmCfgH>(epi, p).cost;
-    half = c128 < c256;
     // Few rows: the kernel made for them, unless these tiles come out ahead,
     // at 1.4 (1.9) us per K step of 256 x 256 (256 x 128) tiles and 4 TB/s of
     // weights.  256 rows: 37,888 x 3584 88 us here and 110 there, 24,576 x 4096
     // 90 and 64, 12,288 x 4096 82 and 58.
-    const double tiles_us = std::max(std::min(1.4 * c256, 1.9 * c128), (double)p.N * p.K * 2.0 / 4e6) + 12.0;
+    const double tiles_us =
+        std::max(std::min(1.4 * p256.cost, 1.9 * p128.cost), (double)p.N * p.K * 2.0 / 4e6) + 12.0;
     const bool narrow = p.N <= 8192 && p.sk_ws && (epi == EPI_STORE || epi == EPI_ACCUM);  // takes K splits there
     if (p.M <= kRowsMax && (p.M <= 128 || narrow || gemm_rows_us(p.M, p.N, p.K) < tiles_us))
       return launch_gemm_rows(epi, p, s);
+    double best = p256.cost;
+    auto consider = [&](TileId id, double cost) {
+      if (cost < best) {
+        best = cost;
+        tile = id;
+      }
+    };
+    consider(TILE_HALF, p128.cost);
+    consider(TILE_N, pn.cost);
+    consider(TILE_M, pm.cost);
+    consider(TILE_S, ps.cost);
   }
-  return half ? launch_plan<GemmCfgH>(epi, p, plan_cfg<GemmCfgH>(epi, p), s)
-              : launch_plan<GemmCfg>(epi, p, plan_cfg<GemmCfg>(epi, p), s);
+  switch (tile) {
+    case TILE_HALF: return launch_plan<GemmCfgH>(epi, p, p128, s);
+    case TILE_N: return launch_plan<GemmCfgN>(epi, p, pn, s);
+    case TILE_M: return launch_plan<GemmCfgM>(epi, p, pm, s);
+    case TILE_S: return launch_plan<GemmCfgS>(epi, p, ps, s);
+    default: return launch_plan<GemmCfg>(epi, p, p256, s);
+  }
 }
 
 }  // namespace acache

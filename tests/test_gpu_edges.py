@@ -151,8 +151,8 @@ def test_linear_few_rows(A, M, N, K, acc):
         got.append(c)
 
 
-@pytest.mark.parametrize("B,blk", [(1, 16), (1, 32), (2, 32), (3, 32), (4, 33), (5, 32), (8, 32), (7, 37)])
-@pytest.mark.parametrize("H,Hkv,F,d", [(4, 4, 1024, 512), (6, 2, 896, 768)])
+@pytest.mark.parametrize("B,blk", [(1, 16), (1, 32), (2, 32), (3, 32), (4, 33), (5, 32), (8, 32), (7, 37), (2, 193), (3, 239)])
+@pytest.mark.parametrize("H,Hkv,F,d", [(4, 4, 1024, 512), (6, 2, 896, 768), (32, 32, 12160, 256), (20, 4, 9472, 512)])
 def test_layer_few_rows(A, B, blk, H, Hkv, F, d):
     """acache_layer_recompute at row counts on both sides of the few-row
     kernel's buckets (16 .. 259 rows): the rotary, K/V store, SwiGLU and
@@ -280,3 +280,27 @@ def test_decode_attention(A, H, Hkv, B, blk, L, k, priv):
     gu = norm(xr, dev["mlp_norm"]) @ D(dev["w_gate_up"]).t()
     xr = xr + (torch.nn.functional.silu(gu[:, :F]) * gu[:, F:]) @ D(dev["w_down"]).t()
     assert_close(down(x), xr.cpu().numpy(), "bf16", "decode rows")
+
+
+# ----------------------------------------------------------------------------- 192-wide tiles
+
+@pytest.mark.parametrize("M,N,K,acc", [
+    (384, 12288, 256, 0),    # 192 x 192 tiles: whole rows and columns
+    (717, 12288, 128, 1),    # a part-full last row tile
+    (600, 8448, 192, 0),     # N a multiple of neither: the last tile's fragments repeat and are skipped
+    (1024, 12288, 64, 1),    # 192 x 256, one K step
+    (1000, 24576, 192, 0),
+    (2048, 12544, 128, 1),
+    (1536, 4096, 256, 0), (4500, 4096, 128, 1),
+])
+def test_linear_tile_shapes(A, M, N, K, acc):
+    a = W.draw_tensor((M, K), "bf16", seed=M)
+    w = W.draw_tensor((N, K), "bf16", std=0.05, seed=N + K)
+    c0 = W.draw_tensor((M, N), "bf16", seed=7)
+    dims = A.make_dims(4096, 32, 32, 128, 256, "bf16")
+    da, dw = up(a, "bf16"), up(w, "bf16")
+    ref = (da.double() @ dw.double().t() + (up(c0, "bf16").double() if acc else 0.0)).cpu().numpy()
+    for work in (None, A.workspace(dims, M, 1, 0)):
+        c = up(c0, "bf16").clone()
+        A.acache_linear(dims, da, dw, out=c, accumulate=bool(acc), ws=work)
+        assert_close(down(c), ref, "bf16", f"linear {M}x{N}x{K} ws {work is not None}")
