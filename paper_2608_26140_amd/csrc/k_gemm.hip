@@ -1060,15 +1060,12 @@ enum TileId { TILE_256, TILE_HALF, TILE_N, TILE_M, TILE_S };
 struct PartialPlan {
   TileId tile;
   int splits;
+  double cost;
 };
 PartialPlan partial_plan(int M, int N, int K) {
-  PartialPlan best = {TILE_256, 1};
-  double best_cost = 1e30;
+  PartialPlan best = {TILE_256, 1, 1e30};
   auto consider = [&](TileId id, int splits, double cost) {
-    if (cost < best_cost) {
-      best_cost = cost;
-      best = {id, splits};
-    }
+    if (cost < best.cost) best = {id, splits, cost};
   };
   double c = 0;
   int s = splits_for<GemmCfg>(M, N, K, &c);
@@ -1081,6 +1078,19 @@ PartialPlan partial_plan(int M, int N, int K) {
   consider(TILE_M, s, c);
   s = splits_for<GemmCfgS>(M, N, K, &c);
   consider(TILE_S, s, c);
+  return best;
+}
+
+// Cost of a stream-K launch on 256 x 256 tiles, on kMaxSkGroups CUs whatever
+// the device: as plan_cfg's, with the stream-K region's K steps 1.3 times as
+// long (its workgroups stand at different K and share less in L2; measured
+// over 24 to 150 tiles there).
+double stream_k_cost(int M, int N, int K) {
+  const int tiles = ((M + 255) / 256) * ((N + 255) / 256), nk = K / 64, G = kMaxSkGroups;
+  const int r = tiles / G, e = tiles % G;
+  if (e == 0) return (double)r * nk;
+  double best = 1e30;
+  for (int g = e; g <= G; ++g) best = std::min(best, (double)r * nk + 1.3 * ((e * nk + g - 1) / g) + (e + g) / 8.0);
   return best;
 }
 
@@ -1200,7 +1210,14 @@ hipError_t launch_plan(GemmEpi epi, const GemmParams& p, const Plan& pl, hipStre
 
 int gemm_bf16_splits(int M, int N, int K) {
   if (M <= kRowsMax) return gemm_rows_splits(M, N, K);
-  return partial_plan(M, N, K).splits;
+  const PartialPlan pp = partial_plan(M, N, K);
+  // One split (the product added to its output by the epilogue) also where
+  // stream-K on 256 x 256 tiles beats the partials by more than what the plan
+  // does not know (its fixup launch).  Down projections with their residual,
+  // us: 9000 rows of 12,288 -> 4096 789 with partials, 656 here; 5000 rows of
+  // 18,944 -> 3584 593 and 520; 10,000 rows 1169 and 1036; but 6352 rows (144
+  // tiles in the stream-K region) 518 and 572.
+  return stream_k_cost(M, N, K) + 10.0 < pp.cost ? 1 : pp.splits;
 }
 
 size_t gemm_bf16_sk_ws_bytes() {
