@@ -593,14 +593,17 @@ acache_status acache_layer_schedule(const acache_dims* dims, int32_t rows, int32
 }
 
 // bf16 block pieces shared by acache_layer_recompute and acache_layer_decode.
-// QKV projection of the normalised rows y with rotary embedding; Q to q, the
-// fresh K/V to their pool slots.
-static acache_status run_qkv_bf16(const acache_dims* dims, const acache_layer_weights* w, int M, const void* y,
-                                  void* q, const int32_t* pos, const int32_t* write_slots, void* k_pool,
+// RMSNorm of the rows x into y and their QKV projection with rotary embedding;
+// Q to q, the fresh K/V to their pool slots.  With mask, the first launch also
+// builds a decode step's key masks.
+static acache_status run_qkv_bf16(const acache_dims* dims, const acache_layer_weights* w, int M, const void* x,
+                                  void* y, void* q, const int32_t* pos, const int32_t* write_slots, void* k_pool,
                                   void* v_pool, int64_t pool_ld, int64_t n_slots, float* part, float* rope,
-                                  hipStream_t stream) {
+                                  hipStream_t stream, int batch = 0, const int32_t* anchors = nullptr, int k = 0,
+                                  int L = 0, uint64_t* mask = nullptr) {
   const int d = dims->d_model, H = dims->n_heads, Hkv = dims->n_kv_heads, dh = dims->head_dim;
-  LAUNCH(launch_rope_table(pos, M, dims->rope_base, rope, stream));
+  LAUNCH_T(ACACHE_K_RMSNORM, stream, launch_layer_begin(x, w->attn_norm, y, M, d, dims->rms_eps, pos, dims->rope_base,
+                                                        rope, batch, anchors, k, L, mask, stream));
   GemmParams g = {};
   g.X = y;
   g.W = w->w_qkv;
@@ -740,9 +743,8 @@ acache_status acache_layer_recompute(const acache_dims* dims, const acache_layer
   }
   bool aff_done = false;
 
-  LAUNCH_T(ACACHE_K_RMSNORM, stream, launch_rmsnorm(dims->dtype, x, w->attn_norm, y, M, d, dims->rms_eps, stream));
   if (dims->dtype == ACACHE_BF16) {
-    st = run_qkv_bf16(dims, w, M, y, q, pos, write_slots, k_pool, v_pool, pool_ld, n_slots, at<float>(ws, p.part),
+    st = run_qkv_bf16(dims, w, M, x, y, q, pos, write_slots, k_pool, v_pool, pool_ld, n_slots, at<float>(ws, p.part),
                       at<float>(ws, p.rope), stream);
     if (st != ACACHE_OK) return st;
     // the part region is idle between the QKV fixup and the O projection
@@ -751,6 +753,7 @@ acache_status acache_layer_recompute(const acache_dims* dims, const acache_layer
                                                                 lse_aff ? score->affix_key_begin : 0, L, &aff_done));
   } else {
     float* qkv = at<float>(ws, p.qkv);
+    LAUNCH_T(ACACHE_K_RMSNORM, stream, launch_rmsnorm(ACACHE_F32, x, w->attn_norm, y, M, d, dims->rms_eps, stream));
     LAUNCH_T(ACACHE_K_GEMM_QKV, stream, launch_gemm_f32((const float*)y, (const float*)w->w_qkv, qkv, nqkv, M, nqkv, d, 0, stream));
     LAUNCH(launch_rope_scatter_f32(qkv, M, H, Hkv, dh, pos, dims->rope_base, (float*)q, write_slots,
                                    (float*)k_pool, (float*)v_pool, pool_ld, n_slots, stream));
@@ -845,9 +848,8 @@ acache_status acache_layer_score(const acache_dims* dims, const acache_layer_wei
     LAUNCH_T(ACACHE_K_RESIDUAL, stream, launch_q_rotary_reduce(g.P, g.splits, Mq, H, score->q_rows, pos,
                                                                dims->rope_base, q, M, stream));
   } else {
-    LAUNCH_T(ACACHE_K_RMSNORM, stream, launch_rmsnorm(dims->dtype, x, w->attn_norm, y, M, d, dims->rms_eps, stream));
     if (dims->dtype == ACACHE_BF16) {
-      st = run_qkv_bf16(dims, w, M, y, q, pos, write_slots, k_pool, v_pool, pool_ld, n_slots, at<float>(ws, p.part),
+      st = run_qkv_bf16(dims, w, M, x, y, q, pos, write_slots, k_pool, v_pool, pool_ld, n_slots, at<float>(ws, p.part),
                         at<float>(ws, p.rope), stream);
       if (st != ACACHE_OK) return st;
       LAUNCH_T(ACACHE_K_ATTENTION, stream, launch_attention_bf16(r, H, Hkv, q, read_slots, k_pool, v_pool, pool_ld,
@@ -855,6 +857,7 @@ acache_status acache_layer_score(const acache_dims* dims, const acache_layer_wei
                                                                   at<float>(ws, p.part), p.part_bytes, stream));
     } else {
       float* qkv = at<float>(ws, p.qkv);
+      LAUNCH_T(ACACHE_K_RMSNORM, stream, launch_rmsnorm(ACACHE_F32, x, w->attn_norm, y, M, d, dims->rms_eps, stream));
       LAUNCH_T(ACACHE_K_GEMM_QKV, stream, launch_gemm_f32((const float*)y, (const float*)w->w_qkv, qkv, nqkv, M, nqkv, d, 0, stream));
       // the pools are written only when the attention reads them (with
       // n_slots 0 no slot is valid and nothing is stored; pos then stands
@@ -914,14 +917,14 @@ acache_status acache_layer_decode(const acache_dims* dims, const acache_layer_we
   void* hb = at<char>(ws, p.h);
   float* part = at<float>(ws, p.part);
 
-  LAUNCH_T(ACACHE_K_RMSNORM, stream, launch_rmsnorm(ACACHE_BF16, x, w->attn_norm, y, M, d, dims->rms_eps, stream));
-  st = run_qkv_bf16(dims, w, M, y, q, pos, write_slots, k_pool, v_pool, pool_ld, n_slots, part, at<float>(ws, p.rope),
-                    stream);
+  uint64_t* mask = affix_len > k ? at<uint64_t>(ws, p.colsum) : nullptr;
+  st = run_qkv_bf16(dims, w, M, x, y, q, pos, write_slots, k_pool, v_pool, pool_ld, n_slots, part, at<float>(ws, p.rope),
+                    stream, batch, anchors, k, affix_len, mask);
   if (st != ACACHE_OK) return st;
   LAUNCH_T(ACACHE_K_ATTENTION, stream,
-           launch_attention_decode_bf16(batch, rows_per_request, H, Hkv, q, affix_slots, affix_len, anchors, k,
-                                        private_slots, private_len, k_pool, v_pool, pool_ld, n_slots, o,
-                                        at<uint64_t>(ws, p.colsum), part, p.part_bytes, stream));
+           launch_attention_decode_bf16(batch, rows_per_request, H, Hkv, q, affix_slots, affix_len, k, private_slots,
+                                        private_len, k_pool, v_pool, pool_ld, n_slots, o, mask, part, p.part_bytes,
+                                        stream));
   return run_out_mlp_bf16(dims, w, M, x, y, o, hb, part, stream);
 }
 

@@ -48,9 +48,13 @@ hipError_t launch_reduce_store(void* c, const float* part, int splits, int M, in
 bool rmsnorm_rows_ok(const void* x, const void* g, const void* y, int d);
 hipError_t launch_rmsnorm_rows(const void* x, int64_t n_src, const int32_t* src_rows, const void* g, void* y,
                                int rows, int d, float eps, hipStream_t s);
-// cos and sin of pos[m] * theta_d for every row m < M and rotary pair d < 64
-// (head_dim 128): table[(m * 64 + d) * 2 + {0, 1}].
-hipError_t launch_rope_table(const int32_t* pos, int M, float rope_base, float* table, hipStream_t s);
+// A bf16 layer's first launch (rmsnorm_rows_ok shapes): y[m] = norm(x[m]);
+// cos and sin of pos[m] * theta_i for every row m < M and rotary pair i < 64
+// (head_dim 128), table[(m * 64 + i) * 2 + {0, 1}]; with mask, the decode
+// step's key masks [batch][ceil(L / 64)] of the anchors [batch][k], L <= 65536.
+hipError_t launch_layer_begin(const void* x, const void* g, void* y, int M, int d, float eps, const int32_t* pos,
+                              float rope_base, float* table, int batch, const int32_t* anchors, int k, int L,
+                              uint64_t* mask, hipStream_t s);
 hipError_t launch_q_rotary_reduce(const float* part, int splits, int n, int H, const int32_t* rows,
                                   const int32_t* pos, float rope_base, void* q, int64_t q_n_rows, hipStream_t s);
 // scores[b, j] (+)= sum over the request's H partial rows of part[b][r][j], in
@@ -76,7 +80,7 @@ struct GemmParams {
   int64_t pool_ld;
   int64_t n_slots;
   const int32_t* write_slots;
-  const float* rope_cs;  // [M][64][2]: cos, sin of row m's rotary angle for pair d (launch_rope_table)
+  const float* rope_cs;  // [M][64][2]: cos, sin of row m's rotary angle for pair d (launch_layer_begin)
   int hq_cols, hkv_cols;
 };
 hipError_t launch_gemm_bf16(GemmEpi epi, const GemmParams& p, hipStream_t s);
@@ -116,15 +120,15 @@ hipError_t launch_attention_bf16(const Ragged& rg, int H, int Hkv, const void* q
                                  float* part, size_t part_bytes, hipStream_t s, float* lse_aff = nullptr,
                                  int aff_begin = 0, int aff_len = 0, bool* aff_done = nullptr);
 // Decode-step attention: the queries of all requests against the shared
-// affix slots (each request's anchors masked out), then each request's
+// affix slots (each request's k anchors masked out), and each request's
 // queries against its private slots, merged.  mask: [batch][ceil(L / 64)]
-// scratch.  Returns hipErrorInvalidValue if part_bytes cannot hold two
-// partial sets.
+// (launch_layer_begin), read where L > k.  Returns hipErrorInvalidValue if
+// part_bytes cannot hold two partial sets.
 hipError_t launch_attention_decode_bf16(int batch, int rows_per_req, int H, int Hkv, const void* q,
-                                        const int32_t* affix_slots, int L, const int32_t* anchors, int k,
+                                        const int32_t* affix_slots, int L, int k,
                                         const int32_t* private_slots, int private_len, const void* k_pool,
                                         const void* v_pool, int64_t pool_ld, int64_t n_slots, void* out,
-                                        uint64_t* mask, float* part, size_t part_bytes, hipStream_t s);
+                                        const uint64_t* mask, float* part, size_t part_bytes, hipStream_t s);
 // Eq. 4-5 for one layer in one launch: part[b][r][j] for r < *rows_per_request
 // (heads x query splits) such that the layer's score of affix key j of
 // request b is the sum over r in order.  row_lse: [q_n_rows, H] natural-log

@@ -1167,29 +1167,11 @@ hipError_t launch_attention_bf16(const Ragged& rg, int H, int Hkv, const void* q
   return hipGetLastError();
 }
 
-// Key masks of the decode step's shared pass: bit j % 64 of word
-// [b][j / 64] is set iff affix-local index j is one of request b's anchors
-// (those positions are read from the request's private slots instead).  One
-// workgroup per request builds its words in LDS.
-__global__ __launch_bounds__(256) void anchor_mask_kernel(const int32_t* __restrict__ anchors, int k, int L,
-                                                          int n_words, uint64_t* __restrict__ mask) {
-  __shared__ unsigned long long words[1024];
-  const int b = blockIdx.x;
-  for (int i = threadIdx.x; i < n_words; i += 256) words[i] = 0ull;
-  __syncthreads();
-  for (int i = threadIdx.x; i < k; i += 256) {
-    const int j = anchors[(int64_t)b * k + i];
-    if (j >= 0 && j < L) atomicOr(&words[j >> 6], 1ull << (j & 63));
-  }
-  __syncthreads();
-  for (int i = threadIdx.x; i < n_words; i += 256) mask[(int64_t)b * n_words + i] = words[i];
-}
-
 hipError_t launch_attention_decode_bf16(int batch, int rows_per_req, int H, int Hkv, const void* q,
-                                        const int32_t* affix_slots, int L, const int32_t* anchors, int k,
+                                        const int32_t* affix_slots, int L, int k,
                                         const int32_t* private_slots, int private_len, const void* k_pool,
                                         const void* v_pool, int64_t pool_ld, int64_t n_slots, void* out,
-                                        uint64_t* mask, float* part, size_t part_bytes, hipStream_t s) {
+                                        const uint64_t* mask, float* part, size_t part_bytes, hipStream_t s) {
   const int64_t rows = (int64_t)batch * rows_per_req;
   if (rows == 0) return hipSuccess;
   const bool shared = L > k;  // some affix position is read from the shared slots
@@ -1259,8 +1241,6 @@ hipError_t launch_attention_decode_bf16(int batch, int rows_per_req, int H, int 
   a.Hkv = Hkv;
   a.rows = (int)rows;
   a.rows_per_req = rows_per_req;
-  if (shared)
-    hipLaunchKernelGGL(anchor_mask_kernel, dim3(batch), dim3(256), 0, s, anchors, k, L, kt_s, mask);
   if (wide) {
     PvArgs pa = {};
     AttnArgs& w = pa.a;

@@ -16,7 +16,7 @@
 // on MFMA 32x32x16 and a ping-pong schedule over 32-wide K units
 // (gemm_bf16_kernel).  Both are fed by buffer -> LDS copies (no staging
 // registers).  The rotary epilogue reads each row's (cos, sin) table,
-// computed once per projection by launch_rope_table.  Workgroups are
+// computed once per layer by launch_layer_begin.  Workgroups are
 // renumbered so that each XCD (8 per chip, own L2) receives a contiguous
 // run of tiles with the M index fastest: the tiles sharing one weight tile
 // run on the same L2.

@@ -144,10 +144,9 @@ __global__ __launch_bounds__(256) void rmsnorm_kernel(const T* __restrict__ x, c
 // rmsnorm_kernel (x * inv * g per element).
 // With rows, output row i normalises x[rows[i]] (the gather fused in; a row
 // index outside [0, n_src) gives a zero row, as the gather does).
-__global__ __launch_bounds__(256) void rmsnorm_vec_kernel(const bf16* __restrict__ x, const bf16* __restrict__ g,
-                                                          bf16* __restrict__ y, int d, float eps,
-                                                          const int32_t* __restrict__ rows, int64_t n_src) {
-  const int64_t row = blockIdx.x;
+__device__ __forceinline__ void rmsnorm_vec_row(int64_t row, const bf16* __restrict__ x, const bf16* __restrict__ g,
+                                                bf16* __restrict__ y, int d, float eps,
+                                                const int32_t* __restrict__ rows, int64_t n_src) {
   int64_t src = row;
   bool ok = true;
   if (rows != nullptr) {
@@ -192,6 +191,56 @@ __global__ __launch_bounds__(256) void rmsnorm_vec_kernel(const bf16* __restrict
       *reinterpret_cast<bf16x8*>(y + row * d + (int64_t)ch * 8) = o;
     }
   }
+}
+
+__global__ __launch_bounds__(256) void rmsnorm_vec_kernel(const bf16* __restrict__ x, const bf16* __restrict__ g,
+                                                          bf16* __restrict__ y, int d, float eps,
+                                                          const int32_t* __restrict__ rows, int64_t n_src) {
+  rmsnorm_vec_row(blockIdx.x, x, g, y, d, eps, rows, n_src);
+}
+
+// ---------------------------------------------------------------- a layer's first launch
+// What a bf16 layer needs before its Q/K/V projection, in one launch, since
+// what bounds each part alone is its launch (a decode step of 32 rows over
+// 8192 affix keys 141 us with three launches and 136 with this one, 4 x 32
+// rows 203 and 197, 32 x 32 rows 805 and 787): the rows' RMSNorm, one workgroup per row; the rotary table, cos and
+// sin of pos[m] * theta_i for 64 pairs, one thread each (the angle in fp64,
+// theta_i = base^(-2i/128), evaluated by rotary_sincos as everywhere else on
+// the path); for a decode step the key masks of its shared keys, one workgroup
+// per request: bit j % 64 of word [b][j / 64] is set iff affix-local index j
+// is one of request b's anchors (those positions are read from the request's
+// private slots instead).
+__global__ __launch_bounds__(256) void layer_begin_kernel(const bf16* __restrict__ x, const bf16* __restrict__ g,
+                                                          bf16* __restrict__ y, int d, float eps, int M,
+                                                          const int32_t* __restrict__ pos, double l2b,
+                                                          float* __restrict__ table, int rope_blocks,
+                                                          const int32_t* __restrict__ anchors, int k, int L,
+                                                          uint64_t* __restrict__ mask) {
+  __shared__ unsigned long long words[1024];
+  int blk = blockIdx.x;
+  if (blk < M) {
+    rmsnorm_vec_row(blk, x, g, y, d, eps, nullptr, 0);
+    return;
+  }
+  blk -= M;
+  if (blk < rope_blocks) {
+    const int64_t i = (int64_t)blk * 256 + threadIdx.x;
+    if (i >= (int64_t)M * 64) return;
+    float sn, cs;
+    rotary_sincos((double)pos[i >> 6] * exp2(-(2.0 * (double)(i & 63) / 128.0) * l2b), &sn, &cs);
+    const float2 v = {cs, sn};
+    reinterpret_cast<float2*>(table)[i] = v;
+    return;
+  }
+  const int b = blk - rope_blocks, n_words = (L + 63) / 64;
+  for (int i = threadIdx.x; i < n_words; i += 256) words[i] = 0ull;
+  __syncthreads();
+  for (int i = threadIdx.x; i < k; i += 256) {
+    const int j = anchors[(int64_t)b * k + i];
+    if (j >= 0 && j < L) atomicOr(&words[j >> 6], 1ull << (j & 63));
+  }
+  __syncthreads();
+  for (int i = threadIdx.x; i < n_words; i += 256) mask[(int64_t)b * n_words + i] = words[i];
 }
 
 // ---------------------------------------------------------------- split-K reduce + rotary (queries only)
@@ -714,26 +763,14 @@ hipError_t launch_reduce_store(void* c, const float* part, int splits, int M, in
   return hipGetLastError();
 }
 
-// ---------------------------------------------------------------- rotary table
-// One thread per (row, pair): the angle pos * theta_d in fp64 (theta_d =
-// base^(-2d/128)), reduced and evaluated by rotary_sincos as everywhere else
-// on the path; the QKV projection's epilogue reads it for all its heads.
-__global__ __launch_bounds__(256) void rope_table_kernel(const int32_t* __restrict__ pos, int M, double l2b,
-                                                         float* __restrict__ table) {
-  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (i >= (int64_t)M * 64) return;
-  const int m = (int)(i >> 6), d = (int)(i & 63);
-  float sn, cs;
-  rotary_sincos((double)pos[m] * exp2(-(2.0 * d / 128.0) * l2b), &sn, &cs);
-  const float2 v = {cs, sn};
-  reinterpret_cast<float2*>(table)[i] = v;
-}
-
-hipError_t launch_rope_table(const int32_t* pos, int M, float rope_base, float* table, hipStream_t s) {
+hipError_t launch_layer_begin(const void* x, const void* g, void* y, int M, int d, float eps, const int32_t* pos,
+                              float rope_base, float* table, int batch, const int32_t* anchors, int k, int L,
+                              uint64_t* mask, hipStream_t s) {
   if (M <= 0) return hipSuccess;
-  const int64_t n = (int64_t)M * 64;
-  hipLaunchKernelGGL(rope_table_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, pos, M,
-                     log2((double)rope_base), table);
+  const int rope_blocks = (int)(((int64_t)M * 64 + 255) / 256);
+  hipLaunchKernelGGL(layer_begin_kernel, dim3((unsigned)M + rope_blocks + (mask ? batch : 0)), dim3(256), 0, s,
+                     (const bf16*)x, (const bf16*)g, (bf16*)y, d, eps, M, pos, log2((double)rope_base), table,
+                     rope_blocks, anchors, k, L, mask);
   return hipGetLastError();
 }
 
