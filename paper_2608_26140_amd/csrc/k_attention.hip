@@ -17,6 +17,7 @@
 // transposing LDS reads.  Softmax runs in base 2 on log2(e)/sqrt(d_h)-
 // prescaled logits (hardware exp2) with a lazy rescale of the running max.
 #include <algorithm>
+#include <type_traits>
 
 #include "device.h"
 #include "internal.h"
@@ -501,46 +502,73 @@ __global__ __launch_bounds__(kPvThreads, 2) void attention_decode_kernel(DecArgs
   }
 }
 
-// Combines the key splits of each (row, head): m = max_s m_s,
-// O = sum_s 2^(m_s - m) O_s / sum_s 2^(m_s - m) l_s.  32 threads per
-// (row, head), 4 dimensions each.  With part_aff also the affix
-// log-sum-exp, log sum_s 2^(a_s) over the splits' shares a_s.
+// Combines the key splits of each (row, head), at most kMergeSplits of them:
+// m = max_s m_s, O = sum_s 2^(m_s - m) O_s / sum_s 2^(m_s - m) l_s, the sums
+// in split order.  32 lanes per (row, head): lane s holds split s's max and
+// sum, and each lane sums 4 dimensions, the O_s of four splits loaded at a
+// time (a chain of one load per split is what bounds it otherwise: 32 rows of
+// 32 heads with 14 splits took 8.9 us so and take 4.6 now, 128 rows of 28
+// heads 11.0 and 6.0).  With part_aff also the affix log-sum-exp, log sum_s 2^(a_s) over the
+// splits' shares a_s.
+constexpr int kMergeSplits = 32;
 __global__ __launch_bounds__(256) void attention_merge_kernel(const float* __restrict__ part_o,
                                                               const float* __restrict__ part_ml, int splits,
                                                               int64_t rows, int H, bf16* __restrict__ out,
                                                               float* __restrict__ lse,
                                                               const float* __restrict__ part_aff,
                                                               float* __restrict__ lse_aff) {
-  const int64_t pair = (int64_t)blockIdx.x * 8 + (threadIdx.x >> 5);
-  if (pair >= rows * H) return;
-  const int c = (threadIdx.x & 31) * 4;
-  float m = -INFINITY;
-  for (int s2 = 0; s2 < splits; ++s2) m = fmaxf(m, part_ml[((int64_t)s2 * rows * H + pair) * 2]);
-  float l = 0.f;
-  f32x4 o = {0.f, 0.f, 0.f, 0.f};
-  for (int s2 = 0; s2 < splits; ++s2) {
-    const float* ml = part_ml + ((int64_t)s2 * rows * H + pair) * 2;
-    const float w = ml[0] == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(ml[0] - m);
-    l += w * ml[1];
-    const f32x4 v = *reinterpret_cast<const f32x4*>(part_o + ((int64_t)s2 * rows * H + pair) * kDh + c);
-#pragma unroll
-    for (int j = 0; j < 4; ++j) o[j] += w * v[j];
+  const int64_t pairs = rows * H, pair = (int64_t)blockIdx.x * 8 + (threadIdx.x >> 5);
+  if (pair >= pairs) return;
+  const int lane = threadIdx.x & 31;
+  float2 ml = {-INFINITY, 0.f};
+  float aff = -INFINITY;
+  if (lane < splits) {
+    ml = *reinterpret_cast<const float2*>(part_ml + (lane * pairs + pair) * 2);
+    if (part_aff) aff = part_aff[lane * pairs + pair];
   }
-  const float inv = 1.f / l;
-  bf16x4 w;
+  const float* po = part_o + pair * kDh + lane * 4;
+  float m = 0.f, w = 0.f, l = 0.f;
+  f32x4 o = {0.f, 0.f, 0.f, 0.f};
+  auto add = [&](auto n_tag, int s0) __attribute__((always_inline)) {
+    constexpr int N = decltype(n_tag)::value;
+    f32x4 v[N];
 #pragma unroll
-  for (int j = 0; j < 4; ++j) w[j] = (bf16)(o[j] * inv);
-  *reinterpret_cast<bf16x4*>(out + pair * kDh + c) = w;
-  if (lse && c == 0) lse[pair] = (m + __log2f(l)) * kLn2;
-  if (part_aff && c == 0) {
-    float ma = -INFINITY;
-    for (int s2 = 0; s2 < splits; ++s2) ma = fmaxf(ma, part_aff[(int64_t)s2 * rows * H + pair]);
-    float la = 0.f;
-    for (int s2 = 0; s2 < splits; ++s2) {
-      const float v = part_aff[(int64_t)s2 * rows * H + pair];
-      la += v == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(v - ma);
+    for (int i = 0; i < N; ++i) v[i] = *reinterpret_cast<const f32x4*>(po + (s0 + i) * pairs * kDh);
+    if (s0 == 0) {  // behind the first loads
+      m = ml.x;
+#pragma unroll
+      for (int st = 16; st > 0; st >>= 1) m = fmaxf(m, __shfl_xor(m, st));
+      w = ml.x == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(ml.x - m);
     }
-    lse_aff[pair] = (ma + __log2f(la)) * kLn2;
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+      const float ws = __shfl(w, s0 + i, 32);
+      l += ws * __shfl(ml.y, s0 + i, 32);
+#pragma unroll
+      for (int j = 0; j < 4; ++j) o[j] += ws * v[i][j];
+    }
+  };
+  int s0 = 0;
+  for (; s0 + 4 <= splits; s0 += 4) add(std::integral_constant<int, 4>{}, s0);
+  if (splits & 2) {
+    add(std::integral_constant<int, 2>{}, s0);
+    s0 += 2;
+  }
+  if (splits & 1) add(std::integral_constant<int, 1>{}, s0);
+  const float inv = 1.f / l;
+  bf16x4 r;
+#pragma unroll
+  for (int j = 0; j < 4; ++j) r[j] = (bf16)(o[j] * inv);
+  *reinterpret_cast<bf16x4*>(out + pair * kDh + lane * 4) = r;
+  if (lse && lane == 0) lse[pair] = (m + __log2f(l)) * kLn2;
+  if (part_aff) {
+    float ma = aff;
+#pragma unroll
+    for (int st = 16; st > 0; st >>= 1) ma = fmaxf(ma, __shfl_xor(ma, st));
+    const float e = aff == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(aff - ma);
+    float la = 0.f;
+    for (int s2 = 0; s2 < splits; ++s2) la += __shfl(e, s2, 32);
+    if (lane == 0) lse_aff[pair] = (ma + __log2f(la)) * kLn2;
   }
 }
 

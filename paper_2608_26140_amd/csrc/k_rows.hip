@@ -3,6 +3,8 @@
 // RMSNorm, and the per-head reduction of probe scores.  All are HBM-bound
 // row copies or row reductions: 16-byte vector accesses, one row per
 // workgroup or grid-stride over 16-byte chunks.
+#include <type_traits>
+
 #include "device.h"
 #include "internal.h"
 
@@ -294,8 +296,8 @@ __global__ __launch_bounds__(256) void q_rotary_reduce_kernel(const float* __res
 // One workgroup per row; each thread keeps NC chunks of 8 columns in
 // registers between the residual sum and the normalisation (d <= 8192).
 // Chunk c of thread t is column chunk t + 256 c; the loads are issued for
-// all NC chunks of a split (clamped to the last chunk, results of absent
-// chunks unused) so that they are in flight together.  Each element is
+// all NC chunks of four splits (clamped to the last chunk, results of absent
+// chunks unused) and the gain so that they are in flight together.  Each element is
 // x + p_0 + p_1 + ... in split order; FRESH: p_0 + p_1 + ..., x not read.
 template <int NC, bool FRESH = false>
 __global__ __launch_bounds__(256) void reduce_residual_kernel(bf16* __restrict__ x, const float* __restrict__ part,
@@ -317,23 +319,39 @@ __global__ __launch_bounds__(256) void reduce_residual_kernel(bf16* __restrict__
 #pragma unroll
     for (int j = 0; j < 8; ++j) v[c][j] = (float)xv[j];
   }
-#pragma unroll 2
-  for (int sp = 0; sp < splits; ++sp) {
-    f32x4 a[NC], b[NC];
+  bf16x8 gv[NC] = {};
+  if (y) {
 #pragma unroll
-    for (int c = 0; c < NC; ++c) {
-      const float* pp = part + (int64_t)sp * M * d + off[c];
-      a[c] = *reinterpret_cast<const f32x4*>(pp);
-      b[c] = *reinterpret_cast<const f32x4*>(pp + 4);
-    }
-#pragma unroll
-    for (int c = 0; c < NC; ++c)
-#pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        v[c][j] += a[c][j];
-        v[c][4 + j] += b[c][j];
-      }
+    for (int c = 0; c < NC; ++c) gv[c] = *reinterpret_cast<const bf16x8*>(g + off[c] - row * d);
   }
+  auto add = [&](auto n_tag, int sp) __attribute__((always_inline)) {
+    constexpr int N = decltype(n_tag)::value;
+    f32x4 a[N][NC], b[N][NC];
+#pragma unroll
+    for (int i = 0; i < N; ++i)
+#pragma unroll
+      for (int c = 0; c < NC; ++c) {
+        const float* pp = part + (int64_t)(sp + i) * M * d + off[c];
+        a[i][c] = *reinterpret_cast<const f32x4*>(pp);
+        b[i][c] = *reinterpret_cast<const f32x4*>(pp + 4);
+      }
+#pragma unroll
+    for (int i = 0; i < N; ++i)
+#pragma unroll
+      for (int c = 0; c < NC; ++c)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          v[c][j] += a[i][c][j];
+          v[c][4 + j] += b[i][c][j];
+        }
+  };
+  int sp = 0;
+  for (; sp + 4 <= splits; sp += 4) add(std::integral_constant<int, 4>{}, sp);
+  if (splits & 2) {
+    add(std::integral_constant<int, 2>{}, sp);
+    sp += 2;
+  }
+  if (splits & 1) add(std::integral_constant<int, 1>{}, sp);
   float ss = 0.f;
 #pragma unroll
   for (int c = 0; c < NC; ++c) {
@@ -358,11 +376,9 @@ __global__ __launch_bounds__(256) void reduce_residual_kernel(bf16* __restrict__
 #pragma unroll
   for (int c = 0; c < NC; ++c) {
     if (ok[c]) {
-      const int ch = threadIdx.x + c * 256;
-      const bf16x8 gv = *reinterpret_cast<const bf16x8*>(g + (int64_t)ch * 8);
       bf16x8 o;
 #pragma unroll
-      for (int j = 0; j < 8; ++j) o[j] = (bf16)(v[c][j] * inv * (float)gv[j]);
+      for (int j = 0; j < 8; ++j) o[j] = (bf16)(v[c][j] * inv * (float)gv[c][j]);
       *reinterpret_cast<bf16x8*>(y + off[c]) = o;
     }
   }
