@@ -120,12 +120,12 @@ def _check(name: str, st: int):
 
 
 def _ptr(t: Optional[torch.Tensor]):
-    return None if t is None else ctypes.c_void_p(t.data_ptr())
+    return None if t is None else t.data_ptr()
 
 
 def _stream(stream=None):
-    s = stream if stream is not None else torch.cuda.current_stream()
-    return ctypes.c_void_p(s.cuda_stream)
+    # with the device's index current_stream skips its search for a device (1 us)
+    return (stream if stream is not None else torch.cuda.current_stream(torch.cuda.current_device())).cuda_stream
 
 
 def _i32(values: Sequence[int]):
