@@ -14,7 +14,8 @@ this counts wait states (one per instruction, k + 1 for s_nop k) and flags
     python -m paper_2608_26140_amd.check_agpr_fences [ASM_FILE]
 
 Without an argument it compiles k_gemm.hip to assembly (hipcc -S) first.
-Exits non-zero and lists the offending lines if it finds any."""
+Reports each tile shape's kernels (one per epilogue); exits non-zero and
+lists the offending lines if it finds any."""
 
 from __future__ import annotations
 
@@ -41,6 +42,12 @@ def kernels(asm: str):
                 out.append((name, cur))
                 cur = None
     return out
+
+
+def tile_of(name: str) -> str:
+    """The tile shape of an instantiation: weight rows x activation rows."""
+    m = re.search(r"(?:Cfg|Tile4)ILi(\d+)ELi(\d+)E", name)
+    return f"{m.group(1)} x {m.group(2)}" if m else name
 
 
 MFMA_WAIT = 19   # wait states from an MFMA to other users of its registers
@@ -145,16 +152,20 @@ def main(argv):
                            check=True, stdout=subprocess.DEVNULL, stderr=subprocess.DEVNULL)
             asm = open(out).read()
     ks = kernels(asm)
-    failed = False
+    tiles = {}  # tile shape -> kernels (one per epilogue), kernels with hazards
     for name, lines in ks:
         bad = unfenced(lines)
+        count = tiles.setdefault(tile_of(name), [0, 0])
+        count[0] += 1
         if bad:
-            failed = True
+            count[1] += 1
             print(f"{name}: {len(bad)} hazards, e.g.")
             for i, t, why in bad[:5]:
                 print(f"  line {i}: {t}  ({why})")
-    print(f"checked {len(ks)} kernels: {'FAIL' if failed else 'ok'}")
-    return 1 if failed else 0
+    for tile, (n, n_bad) in sorted(tiles.items()):
+        print(f"{tile}: checked {n} kernels: {'FAIL' if n_bad else 'ok'}")
+    # every tile shape is built for the same epilogues
+    return 0 if ks and len({n for n, _ in tiles.values()}) == 1 and not any(b for _, b in tiles.values()) else 1
 
 
 if __name__ == "__main__":
