@@ -3,9 +3,10 @@
 //
 // attention_pv_kernel   128 queries per workgroup (4 wavefronts x 32), a
 //                       two-stage LDS ring of 64-key K and V tiles; two
-//                       workgroups per CU.  Optional per-query key masks
-//                       (the decode step's shared pass) and key splits
-//                       merged by attention_merge_kernel.
+//                       workgroups per CU.  Key splits are merged by
+//                       attention_merge_kernel.
+// attention_decode_kernel  the same tiles over a decode step's shared affix,
+//                       with key masks, and its requests' private keys.
 // attention_wide_kernel 256 queries per workgroup (8 wavefronts x 32), a
 //                       four-stage ring filled three tiles ahead, one
 //                       workgroup per CU; for grids that fill whole rounds.
@@ -419,8 +420,8 @@ __global__ __launch_bounds__(kPvThreads, 2) void attention_pv_kernel(PvArgs pa) 
 // launch; with grouped heads the query heads of a KV head are taken as further
 // rows of the tile.  All write (O, max, sum) partials for
 // attention_merge_kernel.  Measured with the merge, before = two launches,
-// the private one unsplit: 1 x 32 rows, 32 heads, 1024 + 717 keys 50 -> 30 us;
-// 4 x 32 rows, 28 heads on 4, 4096 + 1843 keys 91 -> 48 us.
+// the private one unsplit: 1 x 32 rows, 32 heads, 1024 + 717 keys 50 -> 18 us;
+// 4 x 32 rows, 28 heads on 4, 4096 + 1843 keys 91 -> 39 us.
 // Large batches take the shared affix on attention_wide_kernel instead, ahead
 // of a launch with the private workgroups alone, which HBM bounds.
 // ============================================================================

@@ -1,5 +1,6 @@
 // Row-level kernels: gather of recomputed rows, K/V scatter to pool slots,
-// the write/read slot maps, RMSNorm, split-K reduction with residual add and
+// the write/read slot maps, RMSNorm, a layer's first launch (RMSNorm, rotary
+// table, decode key masks), split-K reduction with residual add and
 // RMSNorm, and the per-head reduction of probe scores.  All are HBM-bound
 // row copies or row reductions: 16-byte vector accesses, one row per
 // workgroup or grid-stride over 16-byte chunks.
@@ -204,7 +205,7 @@ __global__ __launch_bounds__(256) void rmsnorm_vec_kernel(const bf16* __restrict
 // ---------------------------------------------------------------- a layer's first launch
 // What a bf16 layer needs before its Q/K/V projection, in one launch, since
 // what bounds each part alone is its launch (a decode step of 32 rows over
-// 8192 affix keys 141 us with three launches and 136 with this one, 4 x 32
+// 1024 affix keys 141 us with three launches and 136 with this one, 4 x 32
 // rows 203 and 197, 32 x 32 rows 805 and 787): the rows' RMSNorm, one workgroup per row; the rotary table, cos and
 // sin of pos[m] * theta_i for 64 pairs, one thread each (the angle in fp64,
 // theta_i = base^(-2i/128), evaluated by rotary_sincos as everywhere else on

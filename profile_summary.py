@@ -42,15 +42,16 @@ ROOT = os.path.dirname(os.path.abspath(__file__))
 # one operation that follow each other directly are one unit (attention's whole-tile and remainder
 # kernels, a GEMM and its stream-K fixup)
 OPERATIONS = {
-    # 256 x 256 tiles run gemm_bf16_w4_kernel (+ gemm_bf16_fixup16), 256 x 128 tiles gemm_bf16_kernel
-    "gemm_gate_up": ([r"gemm_bf16_(w4_)?kernel<4,", r"gemm_bf16_fixup(16)?<4,"], r"gemm_bf16_(w4_)?kernel<4,"),
-    "gemm_qkv": ([r"gemm_bf16_(w4_)?kernel<3,", r"gemm_bf16_fixup(16)?<3,"], r"gemm_bf16_(w4_)?kernel<3,"),
-    "gemm_accum": ([r"gemm_bf16_(w4_)?kernel<1,", r"gemm_bf16_fixup(16)?<1,"], r"gemm_bf16_(w4_)?kernel<1,"),
-    "gemm_partial": ([r"gemm_bf16_(w4_)?kernel<2,"], r"gemm_bf16_(w4_)?kernel<2,"),
-    "attention": ([r"attention_(pv|wide)_kernel", r"attention_merge_kernel"], r"attention_(pv|wide)_kernel"),
+    # 256 and 192 wide tiles run gemm_bf16_w4_kernel (+ gemm_bf16_fixup16), 256 x 128 tiles gemm_bf16_kernel,
+    # few rows gemm_rows_kernel
+    "gemm_gate_up": ([r"gemm_(bf16_|bf16_w4_|rows_)kernel<4,", r"gemm_bf16_fixup(16)?<4,"], r"gemm_(bf16_|bf16_w4_|rows_)kernel<4,"),
+    "gemm_qkv": ([r"gemm_(bf16_|bf16_w4_|rows_)kernel<3,", r"gemm_bf16_fixup(16)?<3,"], r"gemm_(bf16_|bf16_w4_|rows_)kernel<3,"),
+    "gemm_accum": ([r"gemm_(bf16_|bf16_w4_|rows_)kernel<1,", r"gemm_bf16_fixup(16)?<1,"], r"gemm_(bf16_|bf16_w4_|rows_)kernel<1,"),
+    "gemm_partial": ([r"gemm_(bf16_|bf16_w4_|rows_)kernel<2,"], r"gemm_(bf16_|bf16_w4_|rows_)kernel<2,"),
+    "attention": ([r"attention_(pv|wide|decode)_kernel", r"attention_merge_kernel"], r"attention_(pv|wide|decode)_kernel"),
     "score": ([r"score_fused_kernel"], r"score_fused_kernel"),
     "score_reduce": ([r"head_reduce_kernel"], r"head_reduce_kernel"),
-    "rmsnorm": ([r"rmsnorm_vec_kernel", r"rmsnorm_rows_kernel"], r"rmsnorm_(vec|rows)_kernel"),
+    "rmsnorm": ([r"rmsnorm_vec_kernel", r"layer_begin_kernel"], r"(rmsnorm_vec|layer_begin)_kernel"),
     "residual": ([r"reduce_residual_kernel", r"q_rotary_reduce_kernel"], r"(reduce_residual|q_rotary_reduce)_kernel"),
     "gather": ([r"gather_rows_kernel"], r"gather_rows_kernel"),
 }
