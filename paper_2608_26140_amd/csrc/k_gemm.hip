@@ -567,13 +567,13 @@ __device__ __forceinline__ void epilogue16(const GemmParams& p, const f32x4 (&ac
           const float gt = acc[a][b][j], up = acc[a + NA / 2][b][j];
           v[j] = silu_mul(gt, up);
         }
-        store4((bf16*)p.C + (int64_t)m * p.ldc + (g0 + a) * 16 + q4, v);
+        store4((bf16*)p.C + (int64_t)m * p.ldc + (g0 * 16 + q4) + a * 16, v);
       }
     } else if constexpr (EPI == EPI_QKV) {
       // The rotary pairs (d, d + 64) sit in this lane, in fragments a and
       // a + NA / 2.
       const float* rt = p.rope_cs + (int64_t)m * 128;
-      auto rotate = [&](bf16* dst, int a, int d0) {
+      auto rotate = [&](bf16* at, int a, int d0) {
         float lo[4], hi[4];
         const f32x4 t0 = *reinterpret_cast<const f32x4*>(rt + 2 * d0);
         const f32x4 t1 = *reinterpret_cast<const f32x4*>(rt + 2 * d0 + 4);
@@ -585,8 +585,8 @@ __device__ __forceinline__ void epilogue16(const GemmParams& p, const f32x4 (&ac
           lo[j] = x1 * cs - x2 * sn;
           hi[j] = x2 * cs + x1 * sn;
         }
-        store4(dst + d0, lo);
-        store4(dst + d0 + 64, hi);
+        store4(at, lo);
+        store4(at + 64, hi);
       };
       auto plain = [&](bf16* dst, int a) {
         const float v[4] = {acc[a][b][0], acc[a][b][1], acc[a][b][2], acc[a][b][3]};
@@ -606,7 +606,7 @@ __device__ __forceinline__ void epilogue16(const GemmParams& p, const f32x4 (&ac
         }
         if (!is_v) {
 #pragma unroll
-          for (int a = 0; a < 4; ++a) rotate(dst, a, a * 16 + q4);
+          for (int a = 0; a < 4; ++a) rotate(dst + a * 16 + q4, a, a * 16 + q4);
         } else {
 #pragma unroll
           for (int a = 0; a < 8; ++a) plain(dst + a * 16 + q4, a);
@@ -628,7 +628,7 @@ __device__ __forceinline__ void epilogue16(const GemmParams& p, const f32x4 (&ac
             dst = (bf16*)(is_v ? p.v_pool : p.k_pool) + slot * p.pool_ld + c;
           }
           if (!is_v) {
-            rotate(dst, a, d0);
+            rotate(dst + d0, a, d0);
           } else {
             plain(dst + d0, a);
             plain(dst + d0 + 64, a + NA / 2);
