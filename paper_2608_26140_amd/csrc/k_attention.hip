@@ -273,9 +273,10 @@ __device__ __forceinline__ void pv_tiles(const PvPool& kv, char* ring, const int
     // lazy rescale: the running max moves only when exceeded by more than 2^8
     const bool bump = mx > m_run + 8.f;
     if (__builtin_amdgcn_ballot_w64(bump)) {
-      const float m_new = bump ? mx : m_run;
-      const float alpha = __builtin_amdgcn_exp2f(m_run - m_new);
-      m_run = m_new;
+      // 1 where the maximum stays: of a query that has met no key yet both are
+      // -inf, and their difference is no number
+      const float alpha = bump ? __builtin_amdgcn_exp2f(m_run - mx) : 1.f;
+      m_run = bump ? mx : m_run;
       l_part *= alpha;
 #pragma unroll
       for (int d = 0; d < 4; ++d)
@@ -843,9 +844,8 @@ __global__ __launch_bounds__(64 * WAVES, 1) void attention_wide_kernel(PvArgs pa
 #pragma unroll
       for (int qb = 0; qb < QB; ++qb) {
         const bool bp = mx[qb] > m_run[qb] + 8.f;
-        const float m_new = bp ? mx[qb] : m_run[qb];
-        const float alpha = __builtin_amdgcn_exp2f(m_run[qb] - m_new);
-        m_run[qb] = m_new;
+        const float alpha = bp ? __builtin_amdgcn_exp2f(m_run[qb] - mx[qb]) : 1.f;  // see pv_tiles
+        m_run[qb] = bp ? mx[qb] : m_run[qb];
         l_part[qb] *= alpha;
 #pragma unroll
         for (int d = 0; d < 4; ++d)

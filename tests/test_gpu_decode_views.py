@@ -1,0 +1,85 @@
+"""acache_layer_decode over views whose requests share a wavefront: blocks
+that are no multiple of 32 rows, with anchors that cover whole 64-key tiles of
+the affix for one request and not for its neighbours."""
+
+import numpy as np
+import pytest
+
+import workloads as W
+from tests.gpu_util import assert_close, down, up, up_i32
+
+pytestmark = pytest.mark.gpu
+
+DH = 128
+
+
+def anchors_of(pattern, B, L):
+    """[B, k] anchors in whole 64-key tiles; request b covers
+    first   tile 0 if b is even, the last whole tile otherwise;
+    strips  every second tile, from tile b % 2 on (so whichever tile a key
+            split starts at, every second request has no key in it);
+    halves  the first half of the affix or the second (whole splits)."""
+    n = L // 64
+    tiles = []
+    for b in range(B):
+        if pattern == "first":
+            tiles.append([0 if b % 2 == 0 else n - 1])
+        elif pattern == "strips":
+            tiles.append(list(range(b % 2, n - n % 2, 2)))
+        else:
+            tiles.append(list(range(b % 2 * (n // 2), (b % 2 + 1) * (n // 2))))
+    return np.stack([np.concatenate([np.arange(64 * t, 64 * t + 64) for t in ts]) for ts in tiles]).astype(np.int32)
+
+
+@pytest.mark.parametrize("pattern", ["first", "strips", "halves"])
+@pytest.mark.parametrize("H,Hkv,B,blk,L,priv", [
+    (32, 32, 2, 16, 1024, 717),   # one wavefront of two requests
+    (28, 4, 4, 8, 4096, 40),      # four requests a wavefront, grouped heads as further rows
+    (4, 2, 3, 20, 650, 30),       # requests that begin inside a wavefront, a part-full last key tile
+    (4, 4, 8, 16, 1024, 65),
+    (4, 4, 5, 40, 640, 64),
+    (32, 32, 8, 32, 2048, 64),    # whole wavefronts a request: the 256-query kernel
+])
+def test_tiles_masked_for_some(pattern, H, Hkv, B, blk, L, priv):
+    import torch
+    from paper_2608_26140_amd import acache as A
+    rng = np.random.default_rng(L + H + blk)
+    anchors = anchors_of(pattern, B, L)
+    d, F, M, k = 256, 256, B * blk, anchors.shape[1]
+    shapes = dict(w_qkv=((H + 2 * Hkv) * DH, d), w_o=(d, H * DH), w_gate_up=(2 * F, d), w_down=(d, F))
+    dev = {n: up(W.draw_tensor(s, "bf16", std=0.08, seed=i), "bf16") for i, (n, s) in enumerate(shapes.items())}
+    dev["attn_norm"] = dev["mlp_norm"] = up(W.draw_tensor((d,), "bf16", seed=9), "bf16")
+    x0 = up(W.draw_tensor((M, d), "bf16", seed=10), "bf16")
+    n_slots = L + B * priv
+    pools = [up(W.draw_tensor((n_slots, Hkv * DH), "bf16", seed=11 + i), "bf16") for i in range(2)]
+    perm = rng.permutation(n_slots)
+    affix, private = perm[:L], perm[L:].reshape(B, priv)
+    write = private[:, priv - blk:] if priv >= blk else np.full((B, blk), -1)
+    pos = rng.integers(0, 9000, size=M)
+    dims = A.make_dims(d, H, Hkv, DH, F, "bf16")
+    x = x0.clone()
+    A.acache_layer_decode(dims, dev, B, blk, x, up_i32(pos), up_i32(write.reshape(-1)), up_i32(affix),
+                          up_i32(anchors), k, up_i32(private.reshape(-1)), priv, *pools,
+                          A.workspace(dims, M, B, L))
+    # the block in fp64 over each request's own list of keys
+    D = lambda t: t.double()  # noqa: E731
+    norm = lambda t, g: t / torch.sqrt((t * t).mean(1, keepdim=True) + 1e-5) * D(g)  # noqa: E731
+    xr = D(x0)
+    q = (norm(xr, dev["attn_norm"]) @ D(dev["w_qkv"]).t()[:, :H * DH]).view(M, H, DH)
+    th = 10000.0 ** (-2.0 * torch.arange(64, device="cuda", dtype=torch.float64) / DH)
+    an = torch.from_numpy(pos).cuda().double()[:, None, None] * th
+    q = torch.cat([q[..., :64] * an.cos() - q[..., 64:] * an.sin(), q[..., 64:] * an.cos() + q[..., :64] * an.sin()], 2)
+    K, V = (D(p).view(n_slots, Hkv, DH) for p in pools)
+    o = torch.zeros(M, H, DH, dtype=torch.float64, device="cuda")
+    for b in range(B):
+        keep = np.ones(L, bool)
+        keep[anchors[b]] = False
+        sl = torch.from_numpy(np.concatenate([affix[keep], private[b]])).cuda()
+        for h in range(H):
+            g = h // (H // Hkv)
+            lg = q[b * blk:(b + 1) * blk, h] @ K[sl, g].t() / np.sqrt(DH)
+            o[b * blk:(b + 1) * blk, h] = torch.softmax(lg, 1) @ V[sl, g]
+    xr = xr + o.view(M, H * DH) @ D(dev["w_o"]).t()
+    gu = norm(xr, dev["mlp_norm"]) @ D(dev["w_gate_up"]).t()
+    xr = xr + (torch.nn.functional.silu(gu[:, :F]) * gu[:, F:]) @ D(dev["w_down"]).t()
+    assert_close(down(x), xr.cpu().numpy(), "bf16", "decode rows")
