@@ -910,7 +910,6 @@ acache_status acache_layer_decode(const acache_dims* dims, const acache_layer_we
   // the anchor masks live in the scoring region, which a decode step does not use
   const size_t mask_bytes = (size_t)batch * ((affix_len + 63) / 64) * sizeof(uint64_t);
   CHECK(mask_bytes <= (size_t)batch * H * std::max(affix_len, 1) * sizeof(float), ACACHE_ERR_WORKSPACE);
-  CHECK((size_t)M * H * (dh * 4 + 8) * 2 <= p.part_bytes, ACACHE_ERR_WORKSPACE);
   void* y = at<char>(ws, p.y);
   void* q = at<char>(ws, p.q);
   void* o = at<char>(ws, p.o);

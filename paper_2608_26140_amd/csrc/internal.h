@@ -122,8 +122,9 @@ hipError_t launch_attention_bf16(const Ragged& rg, int H, int Hkv, const void* q
 // Decode-step attention: the queries of all requests against the shared
 // affix slots (each request's k anchors masked out), and each request's
 // queries against its private slots, merged.  mask: [batch][ceil(L / 64)]
-// (launch_layer_begin), read where L > k.  Returns hipErrorInvalidValue if
-// part_bytes cannot hold two partial sets.
+// (launch_layer_begin), read where L > k.  Requests whose partials do not fit
+// part_bytes together go one group after the other; hipErrorInvalidValue if
+// not even one row's two partials fit.
 hipError_t launch_attention_decode_bf16(int batch, int rows_per_req, int H, int Hkv, const void* q,
                                         const int32_t* affix_slots, int L, int k,
                                         const int32_t* private_slots, int private_len, const void* k_pool,

@@ -1196,13 +1196,13 @@ hipError_t launch_attention_bf16(const Ragged& rg, int H, int Hkv, const void* q
   return hipGetLastError();
 }
 
-hipError_t launch_attention_decode_bf16(int batch, int rows_per_req, int H, int Hkv, const void* q,
-                                        const int32_t* affix_slots, int L, int k,
-                                        const int32_t* private_slots, int private_len, const void* k_pool,
-                                        const void* v_pool, int64_t pool_ld, int64_t n_slots, void* out,
-                                        const uint64_t* mask, float* part, size_t part_bytes, hipStream_t s) {
+// One group of requests whose partials fit.
+static hipError_t launch_decode_group(int batch, int rows_per_req, int H, int Hkv, const void* q,
+                                      const int32_t* affix_slots, int L, int k, const int32_t* private_slots,
+                                      int private_len, const void* k_pool, const void* v_pool, int64_t pool_ld,
+                                      int64_t n_slots, void* out, const uint64_t* mask, float* part,
+                                      size_t part_bytes, hipStream_t s) {
   const int64_t rows = (int64_t)batch * rows_per_req;
-  if (rows == 0) return hipSuccess;
   const bool shared = L > k;  // some affix position is read from the shared slots
   const bool priv = private_len > 0;
   const int rep = H / Hkv;
@@ -1302,6 +1302,35 @@ hipError_t launch_attention_decode_bf16(int batch, int rows_per_req, int H, int 
   hipLaunchKernelGGL(attention_merge_kernel, dim3((unsigned)((pairs + 7) / 8)), dim3(256), 0, s, (const float*)part,
                      (const float*)a.part_ml, total, rows, H, (bf16*)out, nullptr, nullptr, nullptr);
   return hipGetLastError();
+}
+
+hipError_t launch_attention_decode_bf16(int batch, int rows_per_req, int H, int Hkv, const void* q,
+                                        const int32_t* affix_slots, int L, int k,
+                                        const int32_t* private_slots, int private_len, const void* k_pool,
+                                        const void* v_pool, int64_t pool_ld, int64_t n_slots, void* out,
+                                        const uint64_t* mask, float* part, size_t part_bytes, hipStream_t s) {
+  if (batch == 0 || rows_per_req == 0) return hipSuccess;
+  // The requests in equal groups whose two partial sets (shared and private)
+  // fit; a request that does not fit by itself in slices of its rows.
+  const int64_t fit = (int64_t)(part_bytes / ((size_t)H * (kDh * 4 + 8) * 2));
+  if (fit == 0) return hipErrorInvalidValue;
+  const int per = (int)std::min<int64_t>(batch, std::max<int64_t>(1, fit / rows_per_req));
+  const int groups = (batch + per - 1) / per;
+  // whole 256-query tiles a slice where that many rows fit
+  const int step = rows_per_req <= fit ? rows_per_req : (int)(fit >= 256 ? fit / 256 * 256 : fit);
+  const int words = (L + kTileK - 1) / kTileK;
+  for (int i = 0; i < groups; ++i) {
+    const int b0 = (int)((int64_t)i * batch / groups), nb = (int)((int64_t)(i + 1) * batch / groups) - b0;
+    for (int r0 = 0; r0 < rows_per_req; r0 += step) {
+      const int64_t at = ((int64_t)b0 * rows_per_req + r0) * H * kDh;
+      const hipError_t e = launch_decode_group(
+          nb, std::min(step, rows_per_req - r0), H, Hkv, (const bf16*)q + at, affix_slots, L, k,
+          private_slots ? private_slots + (int64_t)b0 * private_len : nullptr, private_len, k_pool, v_pool, pool_ld,
+          n_slots, (bf16*)out + at, mask ? mask + (int64_t)b0 * words : nullptr, part, part_bytes, s);
+      if (e != hipSuccess) return e;
+    }
+  }
+  return hipSuccess;
 }
 
 

@@ -1,6 +1,7 @@
-"""acache_layer_decode over views whose requests share a wavefront: blocks
+"""acache_layer_decode over views whose requests share a wavefront (blocks
 that are no multiple of 32 rows, with anchors that cover whole 64-key tiles of
-the affix for one request and not for its neighbours."""
+the affix for one request and not for its neighbours), and over more rows than
+the workspace holds attention partials for."""
 
 import numpy as np
 import pytest
@@ -31,20 +32,10 @@ def anchors_of(pattern, B, L):
     return np.stack([np.concatenate([np.arange(64 * t, 64 * t + 64) for t in ts]) for ts in tiles]).astype(np.int32)
 
 
-@pytest.mark.parametrize("pattern", ["first", "strips", "halves"])
-@pytest.mark.parametrize("H,Hkv,B,blk,L,priv", [
-    (32, 32, 2, 16, 1024, 717),   # one wavefront of two requests
-    (28, 4, 4, 8, 4096, 40),      # four requests a wavefront, grouped heads as further rows
-    (4, 2, 3, 20, 650, 30),       # requests that begin inside a wavefront, a part-full last key tile
-    (4, 4, 8, 16, 1024, 65),
-    (4, 4, 5, 40, 640, 64),
-    (32, 32, 8, 32, 2048, 64),    # whole wavefronts a request: the 256-query kernel
-])
-def test_tiles_masked_for_some(pattern, H, Hkv, B, blk, L, priv):
+def check_decode(H, Hkv, B, blk, L, priv, anchors):
     import torch
     from paper_2608_26140_amd import acache as A
     rng = np.random.default_rng(L + H + blk)
-    anchors = anchors_of(pattern, B, L)
     d, F, M, k = 256, 256, B * blk, anchors.shape[1]
     shapes = dict(w_qkv=((H + 2 * Hkv) * DH, d), w_o=(d, H * DH), w_gate_up=(2 * F, d), w_down=(d, F))
     dev = {n: up(W.draw_tensor(s, "bf16", std=0.08, seed=i), "bf16") for i, (n, s) in enumerate(shapes.items())}
@@ -83,3 +74,25 @@ def test_tiles_masked_for_some(pattern, H, Hkv, B, blk, L, priv):
     gu = norm(xr, dev["mlp_norm"]) @ D(dev["w_gate_up"]).t()
     xr = xr + (torch.nn.functional.silu(gu[:, :F]) * gu[:, F:]) @ D(dev["w_down"]).t()
     assert_close(down(x), xr.cpu().numpy(), "bf16", "decode rows")
+
+
+@pytest.mark.parametrize("pattern", ["first", "strips", "halves"])
+@pytest.mark.parametrize("H,Hkv,B,blk,L,priv", [
+    (32, 32, 2, 16, 1024, 717),   # one wavefront of two requests
+    (28, 4, 4, 8, 4096, 40),      # four requests a wavefront, grouped heads as further rows
+    (4, 2, 3, 20, 650, 30),       # requests that begin inside a wavefront, a part-full last key tile
+    (4, 4, 8, 16, 1024, 65),
+    (4, 4, 5, 40, 640, 64),
+    (32, 32, 8, 32, 2048, 64),    # whole wavefronts a request: the 256-query kernel
+])
+def test_tiles_masked_for_some(pattern, H, Hkv, B, blk, L, priv):
+    check_decode(H, Hkv, B, blk, L, priv, anchors_of(pattern, B, L))
+
+
+@pytest.mark.parametrize("H,Hkv,B,blk", [
+    (64, 4, 5, 1801),   # two groups of requests (2 and 3)
+    (64, 4, 3, 5000),   # one request a group
+    (64, 2, 2, 8200),   # a request beyond one group: slices of its rows
+])
+def test_more_rows_than_partials(H, Hkv, B, blk):
+    check_decode(H, Hkv, B, blk, 200, 40, anchors_of("first", B, 200))
