@@ -135,21 +135,10 @@ WsPlan plan_ws(const acache_dims* d, int rows, int batch, int L) {
   w.o = take(M * hq * es);
   w.h = take(M * d->d_ff * es);
   if (d->dtype == ACACHE_BF16) {
-    // largest splits x rows over every row count up to `rows`, so one
-    // workspace serves any smaller call (splits change only at row-tile
-    // boundaries, every one of which is a multiple of 128 rows; up to
-    // kRowsMax rows the partials fit the stream-K space below)
-    size_t part_elems = 0;
-    for (int t = kRowsMax / 128 + 1; (t - 1) * 128 < rows; ++t) {
-      const int m = std::min(rows, t * 128);
-      const int sp = std::max(gemm_bf16_splits(m, d->d_model, (int)hq), gemm_bf16_splits(m, d->d_model, d->d_ff));
-      part_elems = std::max(part_elems, (size_t)sp * (size_t)m * d->d_model);
-      // the query-only projection of the probe's last layer
-      part_elems = std::max(part_elems, (size_t)gemm_bf16_splits(m, (int)hq, d->d_model) * (size_t)m * hq);
-    }
-    // split-K partials of the O / down projections and the stream-K pieces
-    // of the QKV / gate-up projections are never live at the same time
-    w.part_bytes = std::max(part_elems * sizeof(float), gemm_bf16_sk_ws_bytes());
+    // fp32 partials: of the O and down projections and of the query-only
+    // projection of the probe's last layer, of the QKV and gate-up projections
+    // (stream-K) and of the attention, never live at the same time
+    w.part_bytes = gemm_partial_bytes(rows, (int)std::max((size_t)d->d_model, hq));
     w.part = take(w.part_bytes);
     w.qkv = w.gu = 0;
     // the rotary table of the QKV projection: (cos, sin) of 64 pairs per row

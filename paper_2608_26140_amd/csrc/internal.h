@@ -85,6 +85,10 @@ struct GemmParams {
 };
 hipError_t launch_gemm_bf16(GemmEpi epi, const GemmParams& p, hipStream_t s);
 int gemm_bf16_splits(int M, int N, int K);  // split-K choice for EPI_PARTIAL
+// What gemm_bf16_splits keeps its partials (splits x M x N fp32) within, and
+// gemm_bf16_sk_ws_bytes() at least.  Grows with M and with N, so that the space
+// for the most rows and columns serves every product with fewer.
+size_t gemm_partial_bytes(int M, int N);
 // The kernel for few rows (k_gemm_rows.hip), M <= kRowsMax.  Its partials fit
 // gemm_bf16_sk_ws_bytes(); gemm_rows_us: its estimated time unsplit.
 constexpr int kRowsMax = 256;

@@ -1033,16 +1033,18 @@ constexpr bool has_stream_k() {
 // and the launch agree on any device): ceil(T s / G) rounds of ceil(nk / s)
 // steps, plus s fp32 slices of M x N written here and read back by the
 // reduction, about M N 8 / 9.5e6 K steps each at HBM speed.  Splits need not
-// divide nk; each keeps at least kMinSkSteps steps.
+// divide nk; each keeps at least kMinSkSteps steps, and all their partials fit
+// gemm_partial_bytes.
 template <class C>
 int splits_for(int M, int N, int K, double* cost_out) {
   const int tiles = ((M + C::BM - 1) / C::BM) * ((N + C::BN - 1) / C::BN);
   const int nk = K / C::BK;
   const int G = kMaxSkGroups;
   const double slice = (double)M * N * 8.0 / 9.5e6;
+  const size_t set = (size_t)M * N * sizeof(float), space = gemm_partial_bytes(M, N);
   int best = 1;
   double best_cost = 1e30;
-  for (int s = 1; s <= kMaxSplits && nk / s >= kMinSkSteps; ++s) {
+  for (int s = 1; s <= kMaxSplits && nk / s >= kMinSkSteps && s * set <= space; ++s) {
     const double cost =
         (double)((tiles * s + G - 1) / G) * ((nk + s - 1) / s) * step_cost<C>() + s * slice;
     if (cost < best_cost) {
@@ -1224,6 +1226,15 @@ int gemm_bf16_splits(int M, int N, int K) {
 size_t gemm_bf16_sk_ws_bytes() {
   // the 256 x 256 tile's pieces are the larger
   return (size_t)kMaxSkGroups * 2 * GemmCfg::WAVES * 64 * GemmCfg::ACC4 * 4 * sizeof(float);
+}
+
+// Eight splits up to 5120 rows, then splits x rows <= 40,960, one split beyond.
+// No less than the splits that pay for themselves take (two of 20,480 rows the
+// most, over 257 to 70,000 rows and outputs of 512 to 8192 columns): the bound
+// changes none of them.
+size_t gemm_partial_bytes(int M, int N) {
+  const size_t split_rows = std::max<size_t>(M, std::min<size_t>((size_t)M * 8, 40960));
+  return std::max(gemm_bf16_sk_ws_bytes(), split_rows * N * sizeof(float));
 }
 
 hipError_t launch_gemm_bf16(GemmEpi epi, const GemmParams& p, hipStream_t s) {

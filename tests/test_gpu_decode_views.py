@@ -90,9 +90,9 @@ def test_tiles_masked_for_some(pattern, H, Hkv, B, blk, L, priv):
 
 
 @pytest.mark.parametrize("H,Hkv,B,blk", [
-    (64, 4, 5, 1801),   # two groups of requests (2 and 3)
-    (64, 4, 3, 5000),   # one request a group
-    (64, 2, 2, 8200),   # a request beyond one group: slices of its rows
+    (8, 2, 5, 4201),   # 21,005 rows where 20,164 fit: two groups of requests (2 and 3)
+    (8, 2, 3, 11000),  # one request a group
+    (8, 4, 2, 20300),  # a request beyond one group: slices of its rows
 ])
 def test_more_rows_than_partials(H, Hkv, B, blk):
     check_decode(H, Hkv, B, blk, 200, 40, anchors_of("first", B, 200))

@@ -42,3 +42,33 @@ def test_decode_fits_the_size_it_names(A, layer):
                     layer[2] * 128, 1000, p, n, None)
                 assert call(need) == DEVICE, (batch, rows, L)
                 assert call(need - 1) == WORKSPACE
+
+
+@pytest.mark.parametrize("layer", LAYERS)
+def test_a_workspace_serves_fewer_rows(A, layer):
+    """Every row count up to 6000 and a spread up to 40,000: more rows never
+    need less."""
+    dims = _dims(A, layer)
+    rows = list(range(1, 6000)) + list(range(6000, 40000, 37))
+    sizes = [A.acache_workspace_size(dims, r, 4, 1024) for r in rows]
+    shrinks = [(a, b) for a, b, x, y in zip(rows, rows[1:], sizes, sizes[1:]) if y < x]
+    assert not shrinks, shrinks[:3]
+
+
+@pytest.mark.parametrize("layer", LAYERS)
+def test_refresh_and_score_fit_the_size_they_name(A, layer):
+    """acache_layer_recompute and acache_layer_score (the masked rows' queries
+    alone) at row counts on both sides of every 64, with the size named for
+    them and with that of twice the rows."""
+    dims, p = _dims(A, layer), ctypes.c_void_p(256)
+    w = A.LayerWeights(*[256] * 6)
+    for tiles in (1, 2, 3, 4, 5, 9, 24, 36, 72, 80, 85, 106, 128, 145, 200):
+        for rows in (64 * tiles - 1, 64 * tiles, 64 * tiles + 1):
+            cu = (ctypes.c_int32 * 2)(0, rows)
+            rg = A.Ragged(1, cu, (ctypes.c_int32 * 2)(0, rows + 100))
+            sa = A.ScoreArgs(256, cu, 256, 100, A.ACACHE_NORM_AFFIX, 256)
+            for size in (A.acache_workspace_size(dims, rows, 1, 100), A.acache_workspace_size(dims, 2 * rows, 1, 100)):
+                args = (ctypes.byref(dims), ctypes.byref(w), ctypes.byref(rg), p, p, p, p, p, p, layer[2] * 128, 1000)
+                assert A.lib.acache_layer_recompute(*args, None, p, size, None) == DEVICE, rows
+                if layer[3] >= layer[0]:
+                    assert A.lib.acache_layer_score(*args, ctypes.byref(sa), p, size, None) == DEVICE, rows
