@@ -1092,9 +1092,12 @@ double stream_k_cost(int M, int N, int K) {
   const int tiles = ((M + 255) / 256) * ((N + 255) / 256), nk = K / 64, G = kMaxSkGroups;
   const int r = tiles / G, e = tiles % G;
   if (e == 0) return (double)r * nk;
+  // from the most workgroups down, until even whole steps and the fewest
+  // pieces cost more
   double best = 1e30;
-  for (int g = e; g <= G; ++g) best = std::min(best, (double)r * nk + 1.3 * ((e * nk + g - 1) / g) + (e + g) / 8.0);
-  return best;
+  for (int g = G; g >= e && 1.3 * e * nk / g + e / 4.0 < best; --g)
+    best = std::min(best, 1.3 * ((e * nk + g - 1) / g) + (e + g) / 8.0);
+  return (double)r * nk + best;
 }
 
 struct Plan {
@@ -1238,22 +1241,26 @@ size_t gemm_partial_bytes(int M, int N) {
 }
 
 hipError_t launch_gemm_bf16(GemmEpi epi, const GemmParams& p, hipStream_t s) {
-  if (epi == EPI_PARTIAL && p.M <= kRowsMax) return launch_gemm_rows(epi, p, s);
+  // Few rows: the kernel made for them.  From 129 rows on these tiles instead
+  // where they come out ahead, at 1.4 (1.9) us per K step of 256 x 256 (256 x
+  // 128) tiles and 4 TB/s of weights; not asked where that kernel splits K
+  // (partials, and narrow outputs with space for them).  256 rows: 37,888 x
+  // 3584 88 us here and 110 there, 24,576 x 4096 90 and 64, 12,288 x 4096 82
+  // and 58.
+  const bool few = p.M <= kRowsMax;
+  const bool narrow = p.N <= 8192 && p.sk_ws && (epi == EPI_STORE || epi == EPI_ACCUM);
+  if (few && (p.M <= 128 || narrow || epi == EPI_PARTIAL)) return launch_gemm_rows(epi, p, s);
   TileId tile = TILE_256;
   const Plan p256 = plan_cfg<GemmCfg>(epi, p), p128 = plan_cfg<GemmCfgH>(epi, p);
+  if (few) {
+    const double tiles_us =
+        std::max(std::min(1.4 * p256.cost, 1.9 * p128.cost), (double)p.N * p.K * 2.0 / 4e6) + 12.0;
+    if (gemm_rows_us(p.M, p.N, p.K) < tiles_us) return launch_gemm_rows(epi, p, s);
+  }
   const Plan pn = plan_cfg<GemmCfgN>(epi, p), pm = plan_cfg<GemmCfgM>(epi, p), ps = plan_cfg<GemmCfgS>(epi, p);
   if (epi == EPI_PARTIAL) {
     tile = partial_plan(p.M, p.N, p.K).tile;
   } else {
-    // Few rows: the kernel made for them, unless these tiles come out ahead,
-    // at 1.4 (1.9) us per K step of 256 x 256 (256 x 128) tiles and 4 TB/s of
-    // weights.  256 rows: 37,888 x 3584 88 us here and 110 there, 24,576 x 4096
-    // 90 and 64, 12,288 x 4096 82 and 58.
-    const double tiles_us =
-        std::max(std::min(1.4 * p256.cost, 1.9 * p128.cost), (double)p.N * p.K * 2.0 / 4e6) + 12.0;
-    const bool narrow = p.N <= 8192 && p.sk_ws && (epi == EPI_STORE || epi == EPI_ACCUM);  // takes K splits there
-    if (p.M <= kRowsMax && (p.M <= 128 || narrow || gemm_rows_us(p.M, p.N, p.K) < tiles_us))
-      return launch_gemm_rows(epi, p, s);
     double best = p256.cost;
     auto consider = [&](TileId id, double cost) {
       if (cost < best) {
