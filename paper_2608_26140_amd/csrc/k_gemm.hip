@@ -1240,7 +1240,16 @@ size_t gemm_partial_bytes(int M, int N) {
   return std::max(gemm_bf16_sk_ws_bytes(), split_rows * N * sizeof(float));
 }
 
-hipError_t launch_gemm_bf16(GemmEpi epi, const GemmParams& p, hipStream_t s) {
+namespace {
+
+// The kernel a product takes: the one for few rows, or a tile and its plan.
+struct Choice {
+  bool few;
+  TileId tile;
+  Plan plan;
+};
+
+Choice choose(GemmEpi epi, const GemmParams& p) {
   // Few rows: the kernel made for them.  From 129 rows on these tiles instead
   // where they come out ahead, at 1.4 (1.9) us per K step of 256 x 256 (256 x
   // 128) tiles and 4 TB/s of weights; not asked where that kernel splits K
@@ -1249,37 +1258,61 @@ hipError_t launch_gemm_bf16(GemmEpi epi, const GemmParams& p, hipStream_t s) {
   // and 58.
   const bool few = p.M <= kRowsMax;
   const bool narrow = p.N <= 8192 && p.sk_ws && (epi == EPI_STORE || epi == EPI_ACCUM);
-  if (few && (p.M <= 128 || narrow || epi == EPI_PARTIAL)) return launch_gemm_rows(epi, p, s);
-  TileId tile = TILE_256;
+  if (few && (p.M <= 128 || narrow || epi == EPI_PARTIAL)) return {true};
   const Plan p256 = plan_cfg<GemmCfg>(epi, p), p128 = plan_cfg<GemmCfgH>(epi, p);
   if (few) {
     const double tiles_us =
         std::max(std::min(1.4 * p256.cost, 1.9 * p128.cost), (double)p.N * p.K * 2.0 / 4e6) + 12.0;
-    if (gemm_rows_us(p.M, p.N, p.K) < tiles_us) return launch_gemm_rows(epi, p, s);
+    if (gemm_rows_us(p.M, p.N, p.K) < tiles_us) return {true};
   }
+  const Plan* plans[] = {&p256, &p128, nullptr, nullptr, nullptr};  // by TileId
   const Plan pn = plan_cfg<GemmCfgN>(epi, p), pm = plan_cfg<GemmCfgM>(epi, p), ps = plan_cfg<GemmCfgS>(epi, p);
+  plans[TILE_N] = &pn;
+  plans[TILE_M] = &pm;
+  plans[TILE_S] = &ps;
+  TileId tile = TILE_256;
   if (epi == EPI_PARTIAL) {
     tile = partial_plan(p.M, p.N, p.K).tile;
   } else {
-    double best = p256.cost;
-    auto consider = [&](TileId id, double cost) {
-      if (cost < best) {
-        best = cost;
-        tile = id;
-      }
-    };
-    consider(TILE_HALF, p128.cost);
-    consider(TILE_N, pn.cost);
-    consider(TILE_M, pm.cost);
-    consider(TILE_S, ps.cost);
+    for (TileId id : {TILE_HALF, TILE_N, TILE_M, TILE_S})
+      if (plans[id]->cost < plans[tile]->cost) tile = id;
   }
-  switch (tile) {
-    case TILE_HALF: return launch_plan<GemmCfgH>(epi, p, p128, s);
-    case TILE_N: return launch_plan<GemmCfgN>(epi, p, pn, s);
-    case TILE_M: return launch_plan<GemmCfgM>(epi, p, pm, s);
-    case TILE_S: return launch_plan<GemmCfgS>(epi, p, ps, s);
-    default: return launch_plan<GemmCfg>(epi, p, p256, s);
+  return {false, tile, *plans[tile]};
+}
+
+}  // namespace
+
+hipError_t launch_gemm_bf16(GemmEpi epi, const GemmParams& p, hipStream_t s) {
+  const Choice c = choose(epi, p);
+  if (c.few) return launch_gemm_rows(epi, p, s);
+  switch (c.tile) {
+    case TILE_HALF: return launch_plan<GemmCfgH>(epi, p, c.plan, s);
+    case TILE_N: return launch_plan<GemmCfgN>(epi, p, c.plan, s);
+    case TILE_M: return launch_plan<GemmCfgM>(epi, p, c.plan, s);
+    case TILE_S: return launch_plan<GemmCfgS>(epi, p, c.plan, s);
+    default: return launch_plan<GemmCfg>(epi, p, c.plan, s);
   }
 }
 
 }  // namespace acache
+
+// Which kernel a product of M rows, N columns and contraction K takes, for the
+// tests (not part of the ABI): out = weight rows and activation rows of the
+// tile (0, 0: the kernel for few rows), whole rounds of tiles ahead of a
+// stream-K region, tiles in that region.
+extern "C" void acache_gemm_schedule(int32_t epi, int32_t M, int32_t N, int32_t K, int32_t workspace, int32_t* out) {
+  using namespace acache;
+  GemmParams p = {};
+  p.M = M;
+  p.N = N;
+  p.K = K;
+  p.splits = epi == EPI_PARTIAL ? gemm_bf16_splits(M, N, K) : 1;
+  float space;
+  if (workspace) p.sk_ws = &space;  // its presence is all that is asked
+  const Choice c = choose((GemmEpi)epi, p);
+  const int tiles[][2] = {{256, 256}, {256, 128}, {192, 256}, {256, 192}, {192, 192}};  // by TileId
+  out[0] = c.few ? 0 : tiles[c.tile][0];
+  out[1] = c.few ? 0 : tiles[c.tile][1];
+  out[2] = c.plan.sk_tiles > 0 ? c.plan.tm.dp_rounds : 0;
+  out[3] = c.plan.sk_tiles;
+}

@@ -33,13 +33,11 @@ def anchors_of(pattern, B, L):
 
 
 def check_decode(H, Hkv, B, blk, L, priv, anchors):
-    import torch
     from paper_2608_26140_amd import acache as A
+    from tests import block_reference as R
     rng = np.random.default_rng(L + H + blk)
     d, F, M, k = 256, 256, B * blk, anchors.shape[1]
-    shapes = dict(w_qkv=((H + 2 * Hkv) * DH, d), w_o=(d, H * DH), w_gate_up=(2 * F, d), w_down=(d, F))
-    dev = {n: up(W.draw_tensor(s, "bf16", std=0.08, seed=i), "bf16") for i, (n, s) in enumerate(shapes.items())}
-    dev["attn_norm"] = dev["mlp_norm"] = up(W.draw_tensor((d,), "bf16", seed=9), "bf16")
+    dev = R.weights(d, H, Hkv, F)
     x0 = up(W.draw_tensor((M, d), "bf16", seed=10), "bf16")
     n_slots = L + B * priv
     pools = [up(W.draw_tensor((n_slots, Hkv * DH), "bf16", seed=11 + i), "bf16") for i in range(2)]
@@ -52,28 +50,11 @@ def check_decode(H, Hkv, B, blk, L, priv, anchors):
     A.acache_layer_decode(dims, dev, B, blk, x, up_i32(pos), up_i32(write.reshape(-1)), up_i32(affix),
                           up_i32(anchors), k, up_i32(private.reshape(-1)), priv, *pools,
                           A.workspace(dims, M, B, L))
-    # the block in fp64 over each request's own list of keys
-    D = lambda t: t.double()  # noqa: E731
-    norm = lambda t, g: t / torch.sqrt((t * t).mean(1, keepdim=True) + 1e-5) * D(g)  # noqa: E731
-    xr = D(x0)
-    q = (norm(xr, dev["attn_norm"]) @ D(dev["w_qkv"]).t()[:, :H * DH]).view(M, H, DH)
-    th = 10000.0 ** (-2.0 * torch.arange(64, device="cuda", dtype=torch.float64) / DH)
-    an = torch.from_numpy(pos).cuda().double()[:, None, None] * th
-    q = torch.cat([q[..., :64] * an.cos() - q[..., 64:] * an.sin(), q[..., 64:] * an.cos() + q[..., :64] * an.sin()], 2)
-    K, V = (D(p).view(n_slots, Hkv, DH) for p in pools)
-    o = torch.zeros(M, H, DH, dtype=torch.float64, device="cuda")
-    for b in range(B):
-        keep = np.ones(L, bool)
-        keep[anchors[b]] = False
-        sl = torch.from_numpy(np.concatenate([affix[keep], private[b]])).cuda()
-        for h in range(H):
-            g = h // (H // Hkv)
-            lg = q[b * blk:(b + 1) * blk, h] @ K[sl, g].t() / np.sqrt(DH)
-            o[b * blk:(b + 1) * blk, h] = torch.softmax(lg, 1) @ V[sl, g]
-    xr = xr + o.view(M, H * DH) @ D(dev["w_o"]).t()
-    gu = norm(xr, dev["mlp_norm"]) @ D(dev["w_gate_up"]).t()
-    xr = xr + (torch.nn.functional.silu(gu[:, :F]) * gu[:, F:]) @ D(dev["w_down"]).t()
-    assert_close(down(x), xr.cpu().numpy(), "bf16", "decode rows")
+    # the block in fp64 over each request's own list of keys (as stored)
+    views = [np.concatenate([np.delete(affix, anchors[b]), private[b]]) for b in range(B)]
+    q = R.qkv(dev, x0.double(), pos, H, Hkv)[0]
+    ref = R.out_mlp(dev, x0.double(), R.attend(q, *pools, views, blk))
+    assert_close(down(x), ref.cpu().numpy(), "bf16", "decode rows")
 
 
 @pytest.mark.parametrize("pattern", ["first", "strips", "halves"])

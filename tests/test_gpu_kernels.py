@@ -144,16 +144,14 @@ def test_rmsnorm(A, dtype, d):
     assert_close(down(y), ref, dtype, "rmsnorm")
 
 
-# Shapes and the schedule they take with a workspace on 256 CUs with
-# 256 x 256 tiles (T tiles, nk K steps of 64): (256, 3072, 4096) T = 12,
-# stream-K only; (520, 24576, 2048) T = 288, one data-parallel round +
-# stream-K over 32 tiles; (512, 32768, 256) T = 256, data-parallel;
-# (300, 4096, 128) nk = 2, too short for stream-K; (1280, 16384, 64) T = 320
-# and (2304, 8192, 128) T = 288, two data-parallel rounds of one or two K
-# steps, the second partial, on 256 persistent workgroups, so a workgroup's
-# second tile starts right behind its first tile's stores (so does
-# (520, 24576, 2048) without a workspace); the rest run data-parallel by the
-# cost model.
+# What these shapes run on 256 CUs: up to 256 rows the kernel for few rows;
+# (717, 768, 1024) stream-K over nine 256 x 256 tiles with a workspace, 192 x
+# 192 tiles without; (300, 4096, 128) and (520, 24576, 2048) 192 x 192 tiles;
+# (512, 32768, 256) one whole round of 256 x 256 tiles; (1280, 16384, 64) and
+# (2304, 8192, 128) two rounds of 192 x 256 tiles of one or two K steps, the
+# second partial, on 256 persistent workgroups, so a workgroup's second tile
+# starts right behind its first tile's stores.  The stream-K schedules are
+# covered, and held to, by test_gemm_schedules.
 @pytest.mark.parametrize("schedule", ["dp", "sk"])
 @pytest.mark.parametrize("M,N,K", [(1, 256, 64), (77, 512, 256), (128, 256, 4096), (717, 768, 1024), (300, 4096, 128),
                                    (256, 3072, 4096), (520, 24576, 2048), (512, 32768, 256), (1280, 16384, 64),
