@@ -466,7 +466,12 @@ hipError_t launch_gemm_rows(GemmEpi epi, const GemmParams& p, hipStream_t s) {
   // 4096 x 4096 at 32 rows 13 whole, 15 split).
   if ((epi == EPI_STORE || epi == EPI_ACCUM) && p.sk_ws && p.N <= 8192 && p.ldc == p.N) {
     const RowsPlan split = rows_plan(true, p.M, p.N, p.K);
-    if (split.splits > 1 && split.us + 9.f < rows_plan(false, p.M, p.N, p.K).us) {
+    // Above 192 rows the accumulating epilogue waits for the old values of one
+    // 16-row tile after the other, 3 us more than a plain store, and the sum is
+    // cheap up to 2048 columns (512 x 512 at 193 rows 13.3 whole, 10.3 split;
+    // 2048 x 768 16.4 and 12.3; 4096 x 768 at 256 rows 16.5 and 17.0).
+    const float sum = epi == EPI_ACCUM && p.M > 192 && p.N <= 2048 ? 3.f : 9.f;
+    if (split.splits > 1 && split.us + sum < rows_plan(false, p.M, p.N, p.K).us) {
       GemmParams q = p;
       q.splits = split.splits;
       q.P = p.sk_ws;

@@ -94,6 +94,23 @@ def test_linear(M, N, K, want):
 
 
 @pytest.mark.gpu
+@pytest.mark.parametrize("M", [192, 193, 224, 256])
+@pytest.mark.parametrize("N,K", [(256, 1024), (512, 512), (2048, 768), (2304, 768)])
+def test_linear_few_rows_accumulate(M, N, K):
+    """Both sides of the rows and columns from which on a product added to its
+    output goes through K splits sooner."""
+    from paper_2608_26140_amd import acache as A
+    from tests.gpu_util import assert_close, down, up
+    a = up(W.draw_tensor((M, K), "bf16", seed=M), "bf16")
+    w = up(W.draw_tensor((N, K), "bf16", std=0.05, seed=N + K), "bf16")
+    c = up(W.draw_tensor((M, N), "bf16", seed=7), "bf16")
+    dims = A.make_dims(256, 2, 2, 128, 128, "bf16")
+    ref = (a.double() @ w.double().t() + c.double()).cpu().numpy()
+    A.acache_linear(dims, a, w, out=c, accumulate=True, ws=A.workspace(dims, M, 1, 0))
+    assert_close(down(c), ref, "bf16", f"linear {M}x{N}x{K}")
+
+
+@pytest.mark.gpu
 @pytest.mark.parametrize("H,Hkv,d,F,M,qkv,gate_up", LAYERS)
 def test_layer(H, Hkv, d, F, M, qkv, gate_up):
     """The rotary, K/V store and SwiGLU epilogues of those tiles; a row without
