@@ -439,7 +439,9 @@ inline int grid_for(int64_t work, int per_block = 256, int cap = 65535) {
 // with this and 1024 threads (65 MB at 3.0 TB/s).
 constexpr int kArgUnroll = 4;
 
-__device__ __forceinline__ float nan_low(float v) { return fmaxf(v, -INFINITY); }
+// By comparison: a maximum with -inf makes a signalling NaN a quiet one, which
+// the compiler takes a widened bf16 not to be.
+__device__ __forceinline__ float nan_low(float v) { return v == v ? v : -INFINITY; }
 
 // exp(x - m) for x <= m, with x == m giving 1 exactly (also for +inf) and
 // x == -inf giving 0; m > -inf.  bf16 takes +inf as the largest fp32, which

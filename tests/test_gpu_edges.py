@@ -54,6 +54,34 @@ def test_argmax_positions(A, dtype, n):
     np.testing.assert_allclose(conf.cpu().numpy(), O.confidence(x), rtol=2.0 ** -24 * (n / 1024 + 40) + 1e-6, atol=1e-30)
 
 
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("n", [64, 1000, 20000])
+def test_argmax_any_bits(A, dtype, n):
+    """Rows of any bits: NaNs of every kind (quiet, signalling, negative),
+    infinities and denormals.  Confidences within the bound of
+    test_argmax_positions."""
+    import torch
+    rng = np.random.default_rng(n)
+    exp0, snan, ninf = (0x7F, 0x7F81, 0xFF80) if dtype == "bf16" else (0x7FFFFF, 0x7F800001, 0xFF800000)
+    word = 16 if dtype == "bf16" else 32
+    sign = 1 << (word - 1)
+    bits = rng.integers(0, 1 << word, size=(24, n), dtype=np.uint64)
+    bits[:8] = rng.integers(1, exp0 + 1, size=(8, n)) | np.where(rng.random((8, n)) < 0.5, sign, 0)  # denormals
+    bits[8:16] = np.where(rng.random((8, n)) < 0.5, snan, bits[:8])
+    bits[16:20] = np.where(rng.random((4, n)) < 0.9, sign | snan, ninf)  # nothing above -inf
+    bits[20:24, ::3] = snan
+    dev = torch.from_numpy(bits.astype(np.uint16).view(np.int16)).view(torch.bfloat16).cuda() if dtype == "bf16" \
+        else torch.from_numpy(bits.astype(np.uint32).view(np.int32)).cuda().view(torch.float32)
+    wide = bits.astype(np.uint32) << (32 - word)
+    with np.errstate(invalid="ignore"):
+        x = np.where((wide & 0x7FFFFFFF) > 0x7F800000, np.nan, wide.view(np.float32).astype(np.float64))
+        want, want_conf = O.greedy_commit(x), O.confidence(x)
+    conf = torch.full((24,), -1.0, dtype=torch.float32, device="cuda")
+    out = A.acache_argmax_commit(dev, conf=conf)
+    np.testing.assert_array_equal(out.cpu().numpy(), want)
+    np.testing.assert_allclose(conf.cpu().numpy(), want_conf, rtol=2.0 ** -24 * (n / 1024 + 40) + 1e-6, atol=1e-30)
+
+
 # ----------------------------------------------------------------------------- fp32 path
 
 @pytest.mark.parametrize("M,N,K,acc", [
