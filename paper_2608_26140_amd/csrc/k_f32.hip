@@ -301,9 +301,11 @@ __global__ __launch_bounds__(64 * kAttWaves) void attention_f32_kernel(
       }
       m = mt;
     }
+    // a query whose logits were all -inf so far: against 0, which gives zeros
+    const float m_use = m == -INFINITY ? 0.f : m;
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
-      z[r] = expf(z[r] - m);
+      z[r] = expf(z[r] - m_use);
       l += z[r];
     }
     if constexpr (!LSE_ONLY) {

@@ -145,6 +145,35 @@ def test_attention_and_scores_f32_edges(A, H, Hkv, dh):
         assert_close(down(scores), ref, "f32", "scores")
 
 
+@pytest.mark.parametrize("keys,lost", [
+    (65, [64]),                                     # alone in its tile of 16
+    (64, range(16, 32)),                            # all of one wave's keys
+    (300, [*range(0, 48), *range(128, 144), 299]),  # some waves' first tile, others' second
+])
+def test_attention_f32_infinite_logits(A, keys, lost):
+    """Keys with a logit of -inf weigh nothing, whichever wave reads them, and
+    the affix-normalised scores leave them out."""
+    import torch
+    H, dh, rows = 2, 32, 20
+    q = np.abs(W.draw_tensor((rows, H * dh), "f32", seed=1))
+    kp = W.draw_tensor((keys, H * dh), "f32", seed=2)
+    vp = W.draw_tensor((keys, H * dh), "f32", seed=3)
+    kp[list(lost), ::dh] = -np.inf
+    dims = A.make_dims(256, H, H, dh, 128, "f32")
+    slots, lse = up_i32(np.arange(keys)), torch.empty((rows, H), dtype=torch.float32, device="cuda")
+    out = A.acache_attention(dims, [0, rows], [0, keys], up(q, "f32"), slots, up(kp, "f32"), up(vp, "f32"), lse=lse)
+    keep = np.setdiff1d(np.arange(keys), list(lost))
+    heads = lambda t: O.from_bits(t, "f32").reshape(-1, H, dh)  # noqa: E731
+    o_ref, lse_ref = O.attention_via_slots(heads(q), heads(kp), heads(vp), keep, [0, rows], [0, len(keep)])
+    assert_close(down(out), o_ref.reshape(rows, H * dh), "f32", "attention out")
+    assert_close(down(lse), lse_ref, "f32", "attention lse")
+    scores = torch.zeros((1, keys), dtype=torch.float32, device="cuda")
+    A.acache_score(dims, up(q, "f32"), up_i32(np.arange(rows)), [0, rows], up(kp, "f32"), slots, scores)
+    ref = np.zeros((1, keys))
+    ref[0, keep] = O.scores_via_slots(heads(q), np.arange(rows), [0, rows], heads(kp), keep, "affix", None)[0]
+    assert_close(down(scores), ref, "f32", "scores")
+
+
 # ----------------------------------------------------------------------------- bf16 products of few rows
 
 @pytest.mark.parametrize("M", [1, 16, 31, 33, 64, 65, 96, 97, 128, 129, 192, 193, 256, 257])
