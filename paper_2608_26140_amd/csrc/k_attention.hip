@@ -418,7 +418,8 @@ __global__ __launch_bounds__(kPvThreads, 2) void attention_pv_kernel(PvArgs pa) 
 // against a range of its own keys.  A workgroup's time is its chain of tiles
 // (load, logits, softmax, product: 2-3 us each at two workgroups per CU), so
 // both kinds are split along their keys until the CUs are full, and share one
-// launch; with grouped heads the query heads of a KV head are taken as further
+// launch, the kind with the longer workgroups first (32 x 16 rows, 32 heads,
+// 4096 + 1331 keys: the layer 327 us with the two dealt in turn, 276 so); with grouped heads the query heads of a KV head are taken as further
 // rows of the tile.  All write (O, max, sum) partials for
 // attention_merge_kernel.  Measured with the merge, before = two launches,
 // the private one unsplit: 1 x 32 rows, 32 heads, 1024 + 717 keys 50 -> 18 us;
@@ -440,17 +441,17 @@ struct DecArgs {
   int n_shared, n_private;    // workgroups
   int sp_shared, sp_private;  // key splits
   int tiles_shared, tiles_private;  // query tiles per KV head (and request)
+  int shared_first;           // order of the kinds
 };
 
 __global__ __launch_bounds__(kPvThreads, 2) void attention_decode_kernel(DecArgs a) {
   __shared__ __attribute__((aligned(1024))) char ring[2 * kStageB];
-  // XCD-contiguous order, the two kinds dealt in turn
-  const int nb = gridDim.x, i = blockIdx.x;
+  // the kind with the longer workgroups first, each in XCD-contiguous order
+  const int first = a.shared_first ? a.n_shared : a.n_private;
+  const bool shared = ((int)blockIdx.x < first) == (a.shared_first != 0);
+  const int i = (int)blockIdx.x < first ? blockIdx.x : blockIdx.x - first, nb = shared ? a.n_shared : a.n_private;
   const int q8 = nb >> 3, r8 = nb & 7, x = i & 7;
-  const int t = x * q8 + min(x, r8) + (i >> 3);
-  const int before = (int)((int64_t)t * a.n_shared / nb);
-  const bool shared = (int)((int64_t)(t + 1) * a.n_shared / nb) > before;
-  int u = shared ? before : t - before;  // request, KV head, query tile, split
+  int u = x * q8 + min(x, r8) + (i >> 3);  // request, KV head, query tile, split
   const int splits = shared ? a.sp_shared : a.sp_private, tiles = shared ? a.tiles_shared : a.tiles_private;
   const int split = u % splits;
   u /= splits;
@@ -1213,9 +1214,8 @@ static hipError_t launch_decode_group(int batch, int rows_per_req, int H, int Hk
   a.tiles_private = (int)(((int64_t)rows_per_req * rep + kPvTileQ - 1) / kPvTileQ);
   const int64_t wg_s = (int64_t)a.tiles_shared * Hkv, wg_p = (int64_t)batch * a.tiles_private * Hkv;
   // Estimated time (us): 512 workgroups at a time, 3.2 us a tile (2.4 where a
-  // CU has one workgroup), kinds of unequal length ending on average half a
-  // workgroup apart; the private keys at 5 TB/s at best; each split's
-  // partials written and read at 6 TB/s.
+  // CU has one workgroup); the private keys at 5 TB/s at best; each split's
+  // partials written and read at 5 TB/s.
   const double private_us = (double)batch * private_len * Hkv * kRowB * 2.0 / 5e6;
   auto narrow_us = [](int64_t n_s, int len_s, int64_t n_p, int len_p) {
     const int64_t n = n_s + n_p;
@@ -1223,7 +1223,15 @@ static hipError_t launch_decode_group(int batch, int rows_per_req, int H, int Hk
     const int len = std::max(len_s, len_p);
     if (n <= 512) return tile * len;
     if (n_s == 0 || n_p == 0) return tile * len * (double)((n + 511) / 512);
-    return tile * std::max(((double)n_s * len_s + (double)n_p * len_p) / 512.0 + 0.5 * len, (double)len);
+    // the longer kind first; the shorter one fills the slots its last round
+    // leaves, then takes rounds of its own
+    const int64_t n_l = len_s >= len_p ? n_s : n_p;
+    const int shorter = std::min(len_s, len_p);
+    int64_t rest = n - n_l;
+    double t = (double)((n_l + 511) / 512) * len;
+    if (n_l % 512) rest -= (512 - n_l % 512) * (len / shorter);
+    if (rest > 0) t += (double)((rest + 511) / 512) * shorter;
+    return tile * t;
   };
   // The shared affix on the 256-query kernel (2.4 us a tile, one workgroup
   // per CU) in a launch of its own, ahead of the private keys, where that comes
@@ -1240,7 +1248,7 @@ static hipError_t launch_decode_group(int batch, int rows_per_req, int H, int Hk
     for (int sp = priv ? 1 : 0; sp <= (priv ? std::min(16, kt_p) : 0); ++sp) {
       if ((size_t)(per_split * (ss + sp)) > part_bytes) break;
       const int len_s = ss ? (kt_s + ss - 1) / ss : 0, len_p = sp ? (kt_p + sp - 1) / sp : 0;
-      const double merge = 2.0 * per_split * (ss + sp) / 6e6;
+      const double merge = 2.0 * per_split * (ss + sp) / 5e6;
       const double one = std::max(private_us, narrow_us(wg_s * ss, len_s, wg_p * sp, len_p));
       const double two = wide_ok && len_s <= kWdMaskTiles
                              ? 5.0 + 2.4 * (double)((tiles_w * ss + 255) / 256) * len_s +
@@ -1270,6 +1278,8 @@ static hipError_t launch_decode_group(int batch, int rows_per_req, int H, int Hk
   a.Hkv = Hkv;
   a.rows = (int)rows;
   a.rows_per_req = rows_per_req;
+  // by their length in tiles
+  a.shared_first = kt_s * std::max(a.sp_private, 1) >= kt_p * std::max(a.sp_shared, 1);
   if (wide) {
     PvArgs pa = {};
     AttnArgs& w = pa.a;
