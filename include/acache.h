@@ -409,8 +409,9 @@ acache_status acache_rerotate_k(const acache_dims* dims, const void* k_src, cons
  *     positions; the block's own rows are among them).
  * The queries of all requests are taken together against the shared affix
  * keys, so each affix K/V tile is read once per 128 queries rather than once
- * per request; the request's private keys follow, and the two softmax
- * partials are merged.  The result equals acache_layer_recompute over the
+ * per request; the request's private keys are taken beside them, and the
+ * softmax partials are merged (batches whose partials do not fit the
+ * workspace together: one group of requests after the other).  The result equals acache_layer_recompute over the
  * same view up to fp32 summation order.  bf16 only (ACACHE_ERR_UNSUPPORTED
  * otherwise); batch <= 64, affix_len <= 65536.  ws: at least
  * acache_workspace_size(dims, batch * rows_per_request, batch, affix_len)
@@ -491,7 +492,8 @@ typedef enum {
   ACACHE_K_SCORE_LSE = 5,    /* probe: affix-only log-sum-exp (fp32 path; bf16 does it in SCORE_COLSUM) */
   ACACHE_K_SCORE_COLSUM = 6, /* probe: per-head column sums (bf16: with the log-sum-exp sweep) */
   ACACHE_K_SCORE_REDUCE = 7, /* probe: fixed-order head reduction */
-  ACACHE_K_RMSNORM = 8,      /* RMSNorm before attention */
+  ACACHE_K_RMSNORM = 8,      /* RMSNorm before attention (bf16: in one launch with the rotary table and, in a
+                                decode step, the key masks) */
   ACACHE_K_RESIDUAL = 9,     /* split-K reduction + residual (+ RMSNorm) */
   ACACHE_K_TOPK = 10,
   ACACHE_K_GATHER = 11,

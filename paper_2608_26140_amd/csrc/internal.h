@@ -144,7 +144,7 @@ hipError_t launch_score_fused_bf16(int batch, const int* cu_q, int H, int Hkv, c
                                    int64_t n_slots, const int32_t* affix_slots, int L, const float* row_lse,
                                    float* part, size_t part_bytes, int* rows_per_request, hipStream_t s);
 
-// ---- fp32 VALU path (k_f32.hip)
+// ---- fp32 path (k_f32.hip)
 hipError_t launch_gemm_f32(const float* X, const float* W, float* C, int64_t ldc, int M, int N,
                            int K, int accumulate, hipStream_t s);
 hipError_t launch_rope_scatter_f32(const float* qkv, int M, int H, int Hkv, int dh,

@@ -25,6 +25,9 @@
 //   12288 x 4096   M 32: 45 -> 23, 64: 46 -> 27, 128: 47 -> 33, 256: 82 -> 58
 //   37888 x 3584   M 32: 78 -> 48, 64: 83 -> 50, 128: 87 -> 59, 192: 84 -> 70
 //   126464 x 4096  M 32: 233 -> 178 (5.8 TB/s), 128: 256 -> 211, 192: 276 -> 245
+// Above 192 rows a wave's registers are full (2 to 5 spilled, 20 to 37 in the
+// rotary epilogue): still faster than the tiles there (layers of 4096 columns,
+// 224 rows 278 -> 231 us, 256 rows 285 -> 240).
 #include <algorithm>
 #include <type_traits>
 
