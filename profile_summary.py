@@ -1,6 +1,7 @@
 """Summaries of rocprofv3 runs of bench.py for profiles/ (runs on the host, no GPU).
 
     python profile_summary.py stats   RUN_DIR NAME BENCH_JSON OUT_TXT "COMMAND" [--steps N]
+    python profile_summary.py calls   RUN_DIR NAME TITLE CALLS OUT_TXT "COMMAND"
     python profile_summary.py traffic FETCH_CSV WRITE_CSV COPY_FETCH_CSV COPY_WRITE_CSV WORKLOAD OUT_TXT \
                                       "STEP_COMMAND" "COPY_COMMAND" [--steps N] [--copy-mib M]
     python profile_summary.py mfma    PMC_CSV WORKLOAD OUT_TXT "COMMAND" [--steps N]
@@ -9,6 +10,10 @@ stats: the kernel statistics of a `rocprofv3 --kernel-trace --stats` run
 (RUN_DIR/NAME_kernel_stats.csv), and, from its kernel trace, the mean
 duration of the dominant kernel's launches over the run's last N steps
 beside bench.py's HIP-event figure for the same launches.
+
+calls: the kernel statistics of such a run of one call made CALLS times
+(a decode step, say), without bench.py: per kernel its launches and time a
+call.
 
 traffic: HBM bytes per launch of each operation of the step from two
 `--pmc FETCH_SIZE` / `--pmc WRITE_SIZE` passes, scaled by what the same
@@ -145,6 +150,24 @@ def stats(argv):
     print("\n".join(lines[:40]))
 
 
+def calls(argv):
+    run_dir, name, title, n, out, cmd = argv[:6]
+    n = int(n)
+    lines = [f"# rocprofv3 kernel statistics: {title}", "", "command (from the repository root on the GPU box):", f"  {cmd}", "",
+             f"{'kernel':92s} {'a call':>7s} {'avg_us':>9s} {'min_us':>9s} {'us a call':>10s}"]
+    total = 0.0
+    for r in _rows(os.path.join(run_dir, f"{name}_kernel_stats.csv")):
+        if int(r["Calls"]) < n:
+            continue  # setup
+        us = float(r["TotalDurationNs"]) / 1e3 / n
+        total += us
+        lines.append(f"{short(r['Name']):92s} {int(r['Calls']) / n:7.2f} {float(r['AverageNs']) / 1e3:9.2f} "
+                     f"{float(r['MinNs']) / 1e3:9.2f} {us:10.2f}")
+    lines += ["", f"{n} calls; the kernels of a call sum to {total:.1f} us.  Kernels launched fewer times than that belong to the setup."]
+    open(out, "w").write("\n".join(lines) + "\n")
+    print("\n".join(lines))
+
+
 SIMDS = 1024  # 256 CUs x 4 SIMDs
 XCDS = 8
 
@@ -249,4 +272,4 @@ def traffic(argv):
 
 
 if __name__ == "__main__":
-    {"stats": stats, "traffic": traffic, "mfma": mfma}[sys.argv[1]](sys.argv[2:])
+    {"stats": stats, "calls": calls, "traffic": traffic, "mfma": mfma}[sys.argv[1]](sys.argv[2:])
