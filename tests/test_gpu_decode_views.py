@@ -77,3 +77,13 @@ def test_tiles_masked_for_some(pattern, H, Hkv, B, blk, L, priv):
 ])
 def test_more_rows_than_partials(H, Hkv, B, blk):
     check_decode(H, Hkv, B, blk, 200, 40, anchors_of("first", B, 200))
+
+
+@pytest.mark.parametrize("H,Hkv,B,blk,L,priv", [
+    (32, 32, 16, 16, 1024, 40),    # more workgroups than run at a time, the shared ones longer
+    (32, 32, 17, 16, 128, 330),    # the private ones longer
+    (32, 32, 17, 16, 330, 330),    # alike
+    (28, 4, 40, 30, 200, 700),     # grouped heads, the private ones longer
+])
+def test_either_kind_first(H, Hkv, B, blk, L, priv):
+    check_decode(H, Hkv, B, blk, L, priv, anchors_of("first", B, L))
