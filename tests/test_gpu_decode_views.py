@@ -37,7 +37,11 @@ def check_decode(H, Hkv, B, blk, L, priv, anchors):
     from tests import block_reference as R
     rng = np.random.default_rng(L + H + blk)
     d, F, M, k = 256, 256, B * blk, anchors.shape[1]
-    dev = R.weights(d, H, Hkv, F)
+    # standard deviation 0.05: with 0.08 the MLP of single rows amplifies the bf16
+    # rounding of the stored intermediates alone (fp64 arithmetic otherwise; 256
+    # rows over 1024 + 40 keys, row 50) to 0.0328 of the RMS in one element, and
+    # the gate's 8 x RMS error stands at 0.0342 there
+    dev = R.weights(d, H, Hkv, F, std=0.05)
     x0 = up(W.draw_tensor((M, d), "bf16", seed=10), "bf16")
     n_slots = L + B * priv
     pools = [up(W.draw_tensor((n_slots, Hkv * DH), "bf16", seed=11 + i), "bf16") for i in range(2)]
